@@ -31,15 +31,17 @@
  *  - Grid: extents (nx, ny[, nz]), every axis periodic, N = nx*ny[*nz] cells,
  *    linear cell index x + nx*(y + ny*z) (x fastest).
  *  - Populations in the bound buffers, checkpoints and adjoint workspace:
- *    row-blocked, i.e. the Q populations of a group of g consecutive grid
- *    rows are contiguous and population-major inside the group, the g rows
- *    of one population adjacent (g = 2 in 3D when ny is even, else 1):
- *    population i of cell (x, y, z) is element
- *    ((z*ny/g + y/g)*Q*g + i*g + y%g)*rs + x, with the run stride rs = nx
- *    rounded up to a multiple of 32 when nx >= 32 (two-buffer streaming; with
+ *    the Q populations of a group of g consecutive grid rows are contiguous
+ *    and population-major inside the group: population i of cell (x, y, z) is
+ *    element ((z*G + y/g)*Q + i)*p + (y%g)*r + x, with G = ceil(ny/g) groups
+ *    per plane, r elements between the rows of a population run and p between
+ *    its runs.  Rows that are a multiple of 64 cells, or long: r = nx rounded
+ *    up to a multiple of 32, p = g*r, in 3D runs of about 1024 cells (g = 1 in
+ *    2D); else r = nx and p = g*nx rounded up to a multiple of 32 where that
+ *    adds little (two-buffer streaming; with
  *    LBM_STREAM_AA the slot of a value alternates, see lbm_set_streaming).
  *    The layout is internal to the library (sizes from
- *    lbm_workspace_bytes).  In
+ *    lbm_workspace_bytes) and may differ between its builds.  In
  *    LBM_FP64 each element is the double f*_i.  In LBM_FP32_SHIFTED each
  *    element is the float g_i = f*_i - w_i*rho0.  lbm_set_populations and
  *    lbm_get_populations exchange float64 f* in the order [Q][N] (element

@@ -74,6 +74,7 @@ int reduce_blocks(long long N) {
 }
 
 long long step_blocks(ModelId, Prec, const KParams& kp) {
+    if (kp.flat) return static_cast<long long>(kp.nz) * kp.gpp * kp.chunks;
     return static_cast<long long>(kp.ny) * kp.nz / kp.rpb * kp.chunks;
 }
 
@@ -106,11 +107,10 @@ long long run_stride_of(long long nx) {
     const long long a = nx < lbm::kRunAlign ? 1 : lbm::kRunAlign;
     return (nx + a - 1) / a * a + lbm::kRunPad;
 }
-long long run_stride(const lbm_ctx* ctx) { return run_stride_of(ctx->extent[0]); }
 
 size_t pop_bytes(const lbm_ctx* ctx) {
-    return static_cast<size_t>(ctx->N / ctx->extent[0]) * run_stride(ctx) * ctx->Q *
-           elem_bytes(ctx->prec);
+    const KParams& k = ctx->kp;
+    return static_cast<size_t>(k.gs) * k.gpp * k.nz * elem_bytes(ctx->prec);
 }
 
 size_t scratch_bytes(const lbm_ctx* ctx) {
@@ -158,8 +158,82 @@ int initial_form(const lbm_ctx* ctx) { return ctx->aa ? lbm::kFormSwapped : lbm:
 // Blocks of the forward step per slab of the slowest axis (a z-plane in 3D,
 // a row in 2D): the chunk the XCDs take in turn in the alternative mapping.
 int cyclic_chunk(const KParams& k, int D) {
-    const long long blocks = (D == 3 ? static_cast<long long>(k.ny) : 1LL) * k.chunks / k.rpb;
+    const long long rows = D == 3 ? (k.flat ? k.gpp : k.ny) : 1;   // or flat row groups
+    const long long blocks = rows * k.chunks / k.rpb;
     return static_cast<int>(std::max(1LL, std::min(blocks, 1LL << 20)));
+}
+
+// Storage layout (row_base in the kernels).
+//
+// Run length.  A population run holds at least kRunCells cells where the
+// plane has them: one long run per population and group costs HBM less than
+// several short ones (D3Q95 FP32-shifted 128^3, runs of 256 cells against
+// 1024: 304 against 295 us per step, 256^3: 2319 against 2246-2270 us; float64
+// 128^3: 589 against 567 us; 192^3, 320^3 and 384^3 the same within 0.3 %;
+// longer runs give no more).  2D rows are taken one by one: on D2Q33 8192^2
+// groups lost 3 % (2 rows) to 13 % (8 rows).
+//
+// Flat rows.  Rows that are no multiple of a wave and shorter than kFlatCells
+// follow each other without padding, and lanes count through the group: no
+// lane is lost at a row's end, every store of a wave is whole lines, and no
+// padding is read.  Measured against padded rows, whose surplus lanes fill the
+// row's last line (D3Q95 FP32-shifted): 33 cells 72 against 43 us
+// (33x90x80), 100 cells 74 against 64 us (100x75x50), 200 cells 1255 against
+// 1131 us (200^3), 300 cells 665 against 645 us, 415 cells 871 against 875 us:
+// past kFlatCells the padding is small and uniform row addresses cost less.
+// Groups of a power of two of rows leave the last one partly empty; the
+// shortest that keeps the state within the padded rows' bytes (or, for states
+// that are small against the memory, within an eighth of its cells) is taken,
+// else the whole plane is one group.
+constexpr long long kSmallState = 1LL << 30;   // bytes
+
+void fill_layout(const lbm_ctx* ctx, KParams& k) {
+    const long long bytes = static_cast<long long>(elem_bytes(ctx->prec));
+    const long long by_rows = run_stride_of(k.nx) * k.ny;   // elements per population and plane
+    const bool small = by_rows * k.nz * ctx->Q * bytes <= kSmallState;
+    int sh = 0;
+    k.flat = 0;
+    if (k.nx % 64 != 0 && k.nx < lbm::kFlatCells) {
+        while ((static_cast<long long>(k.nx) << sh) < lbm::kRunCells && (1LL << sh) < k.ny) ++sh;
+        for (bool whole = false; !k.flat && !whole; ++sh) {
+            whole = (1LL << sh) >= k.ny;
+            const long long rg = whole ? k.ny : 1LL << sh;
+            const long long gpp = (k.ny + rg - 1) / rg;
+            // whole lines per run, unless that adds more than a sixteenth
+            const long long lines = (rg * k.nx + lbm::kRunAlign - 1) / lbm::kRunAlign;
+            const bool pad = 16 * (lines * lbm::kRunAlign - rg * k.nx) <= rg * k.nx &&
+                             (!whole || lines * lbm::kRunAlign <= by_rows || small);
+            const long long ps = pad ? lines * lbm::kRunAlign : rg * k.nx;
+            const long long plane = ps * gpp * ctx->Q * bytes;
+            const bool fits = ps * gpp <= by_rows ||
+                              (small && (whole || 8 * gpp * rg <= 9LL * k.ny));
+            // the kernels address a plane (in 2D: the grid) with 32-bit byte offsets
+            if (!fits || plane >= (1LL << 32)) continue;
+            k.flat = 1;
+            k.rg = static_cast<int>(rg);
+            k.rg_shift = whole ? 31 : sh;
+            k.rs = k.nx;
+            k.ps = static_cast<int>(ps);
+            k.gpp = static_cast<int>(gpp);
+        }
+    }
+    if (!k.flat) {
+        sh = 0;
+        if (ctx->D == 3)
+            while ((static_cast<long long>(k.nx) << sh) < lbm::kRunCells && k.ny % (2 << sh) == 0)
+                ++sh;
+        k.rs = static_cast<int>(run_stride_of(k.nx));
+        k.rg_shift = sh;
+        k.rg = 1 << sh;
+        k.gpp = k.ny / k.rg;
+        k.ps = k.rg * k.rs;
+    }
+    const int line = lbm::kLineBytes / static_cast<int>(bytes);
+    k.lim = std::min((k.nx + line - 1) / line * line, k.rs);   // unpadded rows: rs = nx
+    // groups and 3D planes stay below 4 GiB
+    k.gs = static_cast<unsigned>(ctx->Q) * static_cast<unsigned>(k.ps);
+    k.zs = ctx->D == 3 ? k.gs * static_cast<unsigned>(k.gpp) : 0u;
+    k.nt = 1;
 }
 
 void fill_kparams(lbm_ctx* ctx) {
@@ -168,10 +242,7 @@ void fill_kparams(lbm_ctx* ctx) {
     k.nx = static_cast<int>(ctx->extent[0]);
     k.ny = static_cast<int>(ctx->extent[1]);
     k.nz = ctx->D == 3 ? static_cast<int>(ctx->extent[2]) : 1;
-    k.rs = static_cast<int>(run_stride(ctx));
-    const bool grouped = ctx->D == 3 && k.ny % lbm::kRowGroup3D == 0;
-    k.rg_shift = grouped ? lbm::kRowGroup3DShift : 0;
-    k.rg = 1 << k.rg_shift;
+    fill_layout(ctx, k);
     k.N = ctx->N;
     const long long rows = static_cast<long long>(k.ny) * k.nz;
     const lbm::RowLaunch rl =
@@ -179,7 +250,13 @@ void fill_kparams(lbm_ctx* ctx) {
     k.chunks = rl.chunks;
     k.bx = rl.bx;
     k.rpb = 1;
-    if (lbm::kPackRows && k.nx % 64 == 0) {
+    if (k.flat) {
+        // the waves of a group, in blocks of equal size
+        const int waves = (k.rg * k.nx + 63) / 64;
+        const int most = lbm::flat_block_limit(ctx->Q, ctx->prec) / 64;
+        k.chunks = (waves + most - 1) / most;
+        k.bx = (waves + k.chunks - 1) / k.chunks * 64;
+    } else if (lbm::kPackRows && k.nx % 64 == 0) {
         // whole rows per block: waves stay inside one row (nx % 64 = 0) and
         // no block is partly empty (rpb divides the row count)
         const int maxb = std::min(lbm::step_max_threads(ctx->model, ctx->prec), lbm::kPackMaxBlock);
@@ -777,6 +854,7 @@ LBM_API int lbm_set_streaming(lbm_ctx* ctx, int scheme) {
         return fail(ctx, LBM_E_INVALID, "scheme must be LBM_STREAM_AB or LBM_STREAM_AA");
     if (ctx->bound) return fail(ctx, LBM_E_STATE, "choose the streaming scheme before lbm_bind");
     ctx->aa = scheme == LBM_STREAM_AA;
+    fill_kparams(ctx);
     ctx->kp.form = initial_form(ctx);
     return LBM_OK;
 }

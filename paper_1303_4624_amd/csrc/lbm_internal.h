@@ -46,16 +46,19 @@ constexpr int kRunPad = LBM_RUN_PAD;
 #endif
 constexpr int kRunAlign = LBM_RUN_ALIGN;
 
-// Rows (consecutive y, same z) whose population runs are interleaved in 3D
-// (a power of two),
-// when ny is a multiple of it (else 1); 2D rows are long enough alone.
-// Measured on D3Q95: 2 rows +0.7 % (FP32-shifted 384^3) and +1.5 % (FP64
-// 256^3); on D2Q33 8192^2 grouping lost 3 % (2 rows) to 13 % (8 rows).
-#ifndef LBM_ROW_GROUP_SHIFT
-#define LBM_ROW_GROUP_SHIFT 1
-#endif
-constexpr int kRowGroup3DShift = LBM_ROW_GROUP_SHIFT;
-constexpr int kRowGroup3D = 1 << kRowGroup3DShift;
+constexpr int kLineBytes = 128;   // a cache line
+
+// Cells of a population run of a row group in 3D, and rows below which (when
+// no multiple of a wave) a group is stored flat; see fill_layout in
+// lbm_api.cpp.  2D rows are long enough alone: on D2Q33 8192^2 groups lost
+// 3 % (2 rows) to 13 % (8 rows).
+constexpr int kRunCells = 1024;
+constexpr int kFlatCells = 384;
+
+// Threads per block of the kernels on flat groups: float64 with the
+// 4th-order sets 128 (D3Q95 200^3: 2192 us per step, 256 threads 2231 us),
+// else 256 (FP32-shifted: the same within 1 % with 128).
+constexpr int flat_block_limit(int Q, Prec p) { return (p == Prec::F64 && Q >= 33) ? 128 : 256; }
 
 // Whole grid rows per block of the row-blocked kernels when a row is a
 // multiple of 64 cells and several fit in one block (0: one row per block).
@@ -95,10 +98,18 @@ constexpr int kFormPushed = 2;    // in place, after an odd number of steps: run
 struct KParams {
     int nx, ny, nz;           // nz = 1 in 2D
     int form;                 // storage form of the state the kernel reads or writes
-    int rs;                   // run stride: elements between two population runs of a row
-    int rg;                   // rows per group (consecutive y sharing interleaved runs), 1 or 2
-    int rg_shift;             // log2(rg)
-    int chunks;               // blocks per grid row (x direction)
+    int rs;                   // elements between two rows of a population run
+    int lim;                  // by rows: elements of a row a step writes (cells, then padding
+                              // to the end of the last line)
+    int rg;                   // rows per group (consecutive y whose runs are adjacent)
+    int rg_shift;             // log2(rg); 31 when a group is the whole plane
+    int ps;                   // elements of a population run of a group
+    unsigned gs;              // elements of a group, Q*ps
+    unsigned zs;              // elements of a plane in 3D, 0 in 2D (one plane)
+    int flat;                 // 1: lanes take the cells of a row group in x-fastest order
+    int nt;                   // 1: non-temporal stores
+    int gpp;                  // row groups per plane
+    int chunks;               // blocks per grid row (x direction); flat: per row group
     int rpb;                  // grid rows per block (> 1 only with chunks = 1, nx % 64 = 0)
     int bx;                   // threads per block (multiple of 64)
     int xcd_cyclic;           // > 0: the forward steps hand the 8 XCDs chunks of this

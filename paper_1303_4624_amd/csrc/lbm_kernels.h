@@ -8,10 +8,12 @@
 // Data layout: row-blocked.  The Q populations of a group of consecutive
 // grid rows are contiguous, population-major (see PopAt / row_base), cells
 // x-fastest.  One thread owns one cell and a block one grid row (or a chunk
-// of it, or several whole rows of 64j cells).  Every population read is a contiguous run of a source row
-// (neighbouring threads read neighbouring x), so the gather f_i(x - e_i) is
-// coalesced; the x-wrap of the periodic grid is folded into a per-lane
-// offset, the y/z-wrap into wave-uniform slab bases and row offsets.
+// of it, or several whole rows of 64j cells); where rows are short and no
+// multiple of a wave, a block owns consecutive cells of a row group (FLAT).
+// Every population read is a contiguous run of a source row (neighbouring
+// threads read neighbouring x), so the gather f_i(x - e_i) is coalesced; the
+// x-wrap of the periodic grid is folded into a per-lane offset, the y/z-wrap
+// into wave-uniform slab bases and row offsets (FLAT: the y-wrap per lane).
 //
 // Precision variants:
 //   F64  : f_i stored and computed in float64.
@@ -111,6 +113,7 @@ struct F64T {
     static constexpr bool shifted = false;
     static constexpr int waves = 1;
     static constexpr int adj_waves = 1;
+    static constexpr int aa_waves = 1;
 };
 struct F32ST {
     using S = float;
@@ -126,6 +129,7 @@ struct F32ST {
     static constexpr bool shifted = true;
     static constexpr int waves = LBM_F32_WAVES;
     static constexpr int adj_waves = LBM_ADJ_WAVES;
+    static constexpr int aa_waves = 3;   // in-place steps that fit 168 VGPRs
 };
 
 template <Prec P>
@@ -149,31 +153,34 @@ __device__ __forceinline__ int wrap_idx(int v, int n) {
 }
 
 struct Cell {
-    int x, y, z;        // x clamped into the grid for inactive lanes
-    int row;            // y + ny*z
-    bool active;
+    int x, y, z;        // the cell; lanes that own none take the last cell of their run
+    int at;             // element of the population run the lane stores to
+    bool active;        // the lane owns a cell
+    bool idle;          // it owns neither a cell nor a padding element of the run
     long long c;        // linear cell index
 };
 
 // Storage layout of the populations: the Q populations of a group of rg
-// consecutive grid rows (fixed z; rg = 1 in 2D) are contiguous,
-// population-major, the rg rows of one population adjacent: population i
-// of cell (x, y, z) sits at row_base(y, z) + i*rg*rs + x, rs >= nx the run
-// stride (KParams::rs, KParams::rg).  A step then writes contiguous runs per
-// row and reads Q runs from the few source rows around it.
+// consecutive grid rows (fixed z) are contiguous, population-major:
+// population i of cell (x, y, z) sits at row_base(y, z) + i*ps + x.  ps is the
+// length of a population run (the group's rows of one population, each rs
+// elements after the previous), of whole 128-byte lines unless that would pad
+// a small run by much (fill_layout in lbm_api.cpp); a group holds
+// gs = Q*ps elements and a plane zs (KParams).  A step then writes contiguous
+// runs and reads Q runs from the few source rows around it.
+//   by rows : rs = nx rounded up to whole lines, rg = 1 or 2, ps = rg*rs.
+//   flat    : rs = nx (no gaps between the rows of a run), rg a power of two
+//             or the whole plane, ps = rg*nx rounded up to whole lines.
 //
 // Where population i of cell c is stored depends on the form of the state
 // (KParams::form): kFormAB, run i of cell c; kFormSwapped (in-place AA
 // pattern after an even number of steps), run opp(i) of cell c;
 // kFormPushed (AA after an odd number), run i of cell c + e_i.
-// Element offset of the first population run of grid row (y, z): rows are
-// taken in groups of rg consecutive y (same z) whose runs interleave, so a
-// population run of a group is rg*rs elements long.
-__device__ __forceinline__ long long row_base(const KParams& k, int Q, int y, int z) {
+// Element offset of the first population run of grid row (y, z).
+__device__ __forceinline__ long long row_base(const KParams& k, int y, int z) {
     const int gy = y >> k.rg_shift;
     const int ry = y - (gy << k.rg_shift);
-    return (static_cast<long long>(z) * k.ny * Q + static_cast<long long>(gy) * Q * k.rg + ry) *
-           k.rs;
+    return static_cast<long long>(z) * k.zs + static_cast<long long>(gy) * k.gs + ry * k.rs;
 }
 
 // Element index of population i of cell c in storage form FORM (a
@@ -196,8 +203,8 @@ struct PopAt {
     __device__ __forceinline__ PopAt(const KParams& k, long long c) {
         int x, y, z;
         cell_xyz(k, c, x, y, z);
-        pstride = static_cast<long long>(k.rg) * k.rs;
-        base = row_base(k, M::Q, y, z) + x;
+        pstride = k.ps;
+        base = row_base(k, y, z) + x;
     }
     template <int i>
     __device__ __forceinline__ long long at() const {
@@ -214,13 +221,13 @@ struct PopAt<M, kFormPushed> {
     __device__ __forceinline__ PopAt(const KParams& k, long long c) {
         int x, y, z;
         cell_xyz(k, c, x, y, z);
-        pstride = static_cast<long long>(k.rg) * k.rs;
+        pstride = k.ps;
         static_for<kW>([&](auto DI) {
             constexpr int d = decltype(DI)::value - kMaxDisp;
             xo[d + kMaxDisp] = wrap_idx(x + d, k.nx);
-            yo[d + kMaxDisp] = row_base(k, M::Q, wrap_idx(y + d, k.ny), 0);
+            yo[d + kMaxDisp] = row_base(k, wrap_idx(y + d, k.ny), 0);
             zo[d + kMaxDisp] =
-                (M::D == 3) ? static_cast<long long>(wrap_idx(z + d, k.nz)) * k.ny * M::Q * k.rs : 0;
+                (M::D == 3) ? static_cast<long long>(wrap_idx(z + d, k.nz)) * k.zs : 0;
         });
     }
     template <int i>
@@ -230,8 +237,16 @@ struct PopAt<M, kFormPushed> {
     }
 };
 
-// Row-blocked mapping: block b covers threads [chunk*bx, chunk*bx + bx) of
-// grid row `row` = y + ny*z.  y and z are uniform over the block.
+// Cell of a lane.  By rows: block b covers threads [chunk*bx, chunk*bx + bx) of
+// grid row y + ny*z (or rpb whole rows); y and z are uniform over a wave.
+// FLAT: block b covers bx cells, x fastest, of one row group (see row_base);
+// z is uniform over the block, y per lane.
+// Lanes past the cells of their run take the elements of its last 128-byte
+// line, so that a step writes whole lines only: a partly written line costs
+// more than a whole one in HBM, non-temporal stores above all (D3Q95
+// FP32-shifted 150^3: 661 us per step with the surplus lanes storing to the
+// row's first cell, 509 us with them filling the line).  Lanes past that are
+// idle.
 // Blocks are dispatched round-robin over the 8 XCDs.  By default each XCD
 // takes a contiguous range of rows, so the chunks of a row share one L2.
 // CYCLIC (the forward steps, which sum nothing across blocks, so the mapping
@@ -239,7 +254,7 @@ struct PopAt<M, kFormPushed> {
 // 8 * xcd_cyclic blocks, the XCDs take chunks of xcd_cyclic blocks in turn
 // instead.  Which of the two is faster depends on where the buffers lie in
 // HBM (lbm_tune_step measures it).
-template <bool CYCLIC = false>
+template <bool FLAT, class S, bool CYCLIC = false>
 __device__ __forceinline__ Cell row_cell(const KParams& k) {
 #if LBM_XCD_REMAP
     const int hb = blockIdx.x;
@@ -256,63 +271,88 @@ __device__ __forceinline__ Cell row_cell(const KParams& k) {
 #else
     const int b = blockIdx.x;
 #endif
-    int row, x;
-    if (kPackRows && k.rpb > 1) {
-        // rpb whole rows of nx (a multiple of 64) lanes: the row is uniform
-        // over each wave
-        const int sub = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / k.nx);
-        row = b * k.rpb + sub;
-        x = static_cast<int>(threadIdx.x) - sub * k.nx;
-    } else {
-        const int chunk = b % k.chunks;
-        row = b / k.chunks;
-        x = chunk * k.bx + static_cast<int>(threadIdx.x);
-    }
     Cell cl;
-    cl.active = x < k.nx;
-    cl.x = cl.active ? x : 0;
-    cl.row = row;
-    cl.y = row % k.ny;
-    cl.z = row / k.ny;
-    cl.c = (static_cast<long long>(row)) * k.nx + cl.x;
+    if constexpr (FLAT) {
+        const int gi = b / k.chunks;
+        const int z = gi / k.gpp, y0 = (gi - z * k.gpp) << k.rg_shift;
+        const int cells = (k.ny - y0 < k.rg ? k.ny - y0 : k.rg) * k.nx;
+        const int j = (b - gi * k.chunks) * k.bx + static_cast<int>(threadIdx.x);
+        constexpr int line = kLineBytes / static_cast<int>(sizeof(S));
+        const int whole = (cells + line - 1) / line * line;
+        const int lim = whole < k.ps ? whole : k.ps;
+        cl.active = j < cells;
+        cl.idle = j >= lim;
+        cl.at = cl.idle ? lim - 1 : j;
+        const unsigned jc = static_cast<unsigned>(cl.active ? j : cells - 1);
+        const unsigned r = jc / static_cast<unsigned>(k.nx);
+        cl.x = static_cast<int>(jc - r * static_cast<unsigned>(k.nx));
+        cl.y = y0 + static_cast<int>(r);
+        cl.z = z;
+        cl.c = (static_cast<long long>(z) * k.ny + y0) * k.nx + jc;
+    } else {
+        int row, x;
+        if (kPackRows && k.rpb > 1) {
+            // rpb whole rows of nx (a multiple of 64) lanes: the row is uniform
+            // over each wave
+            const int sub = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / k.nx);
+            row = b * k.rpb + sub;
+            x = static_cast<int>(threadIdx.x) - sub * k.nx;
+        } else {
+            const int chunk = b % k.chunks;
+            row = b / k.chunks;
+            x = chunk * k.bx + static_cast<int>(threadIdx.x);
+        }
+        cl.active = x < k.nx;
+        cl.idle = x >= k.lim;
+        cl.x = cl.active ? x : k.nx - 1;
+        cl.at = cl.idle ? k.lim - 1 : x;
+        cl.y = row % k.ny;
+        cl.z = row / k.ny;
+        cl.c = static_cast<long long>(row) * k.nx + cl.x;
+    }
     return cl;
 }
 
 // Addresses around one cell: a 64-bit base per slab of the slowest axis
-// (z-planes in 3D, rows in 2D; wave-uniform) plus a 32-bit byte offset inside
-// the slab (row, population run, x).  A slab stays below 4 GiB (checked on
-// the host).  at<slot, dx, dy, dz>() is the address of population run `slot`
+// (planes in 3D and FLAT, rows in 2D; wave-uniform) plus a 32-bit byte offset
+// inside the slab (row, population run, x).  A slab stays below 4 GiB (checked
+// on the host).  at<slot, dx, dy, dz>() is the address of population run `slot`
 // of cell (x + dx, y + dy, z + dz), periodic; |d| <= kMaxDisp.
-template <class M, class S, class B>
+// OWN (the in-place kernels, which store through these addresses): a lane on
+// the padding of a run keeps to that padding instead of wrapping.
+template <class M, class S, class B, bool FLAT, bool OWN>
 struct SlabAddr {
+    static constexpr bool planes = M::D == 3 || FLAT;
     unsigned runb;
     unsigned xb[kW], yb[kW];
     B* sb[kW];
     __device__ __forceinline__ SlabAddr(B* base, const KParams& k, const Cell& cl) {
-        const unsigned rsb = static_cast<unsigned>(k.rs) * static_cast<unsigned>(sizeof(S));
-        runb = rsb * static_cast<unsigned>(k.rg);
-        const unsigned groupb = runb * static_cast<unsigned>(M::Q);   // one row group
+        constexpr unsigned w = static_cast<unsigned>(sizeof(S));
+        const unsigned rsb = static_cast<unsigned>(k.rs) * w;
+        runb = static_cast<unsigned>(k.ps) * w;
+        const bool pad = OWN && !cl.active;
         static_for<kW>([&](auto DI) {
             constexpr int d = decltype(DI)::value - kMaxDisp;   // table entry d: cell at -d
-            xb[d + kMaxDisp] = static_cast<unsigned>(wrap_idx(cl.x - d, k.nx)) * sizeof(S);
-            const int yr = wrap_idx(cl.y - d, k.ny);
-            const int gy = yr >> k.rg_shift, ry = yr - (gy << k.rg_shift);
-            const unsigned inslab = static_cast<unsigned>(gy) * groupb + static_cast<unsigned>(ry) * rsb;
-            if constexpr (M::D == 3) {
-                yb[d + kMaxDisp] = inslab;
-                sb[d + kMaxDisp] = base + static_cast<unsigned long long>(wrap_idx(cl.z - d, k.nz)) *
-                                              (static_cast<unsigned long long>(rsb) * M::Q * k.ny);
+            xb[d + kMaxDisp] = static_cast<unsigned>(pad ? cl.at : wrap_idx(cl.x - d, k.nx)) * w;
+            const int yr = FLAT && pad ? cl.y : wrap_idx(cl.y - d, k.ny);
+            const int gy = yr >> k.rg_shift;
+            const int ry = FLAT && pad ? 0 : yr - (gy << k.rg_shift);
+            if constexpr (planes) {
+                yb[d + kMaxDisp] =
+                    static_cast<unsigned>(gy) * (k.gs * w) + static_cast<unsigned>(ry) * rsb;
+                sb[d + kMaxDisp] =
+                    base + static_cast<unsigned long long>(wrap_idx(cl.z - d, k.nz)) * (k.zs * w);
             } else {
                 yb[d + kMaxDisp] = 0u;
-                sb[d + kMaxDisp] = base + static_cast<unsigned long long>(gy) * groupb +
+                sb[d + kMaxDisp] = base + static_cast<unsigned long long>(gy) * (k.gs * w) +
                                    static_cast<unsigned long long>(ry) * rsb;
             }
         });
     }
-    template <int slot, int dx, int dy, int dz>
+template <int slot, int dx, int dy, int dz>
     __device__ __forceinline__ B* at() const {
-        constexpr int ds = (M::D == 3) ? dz : dy;      // along the slab axis
-        constexpr int dr = (M::D == 3) ? dy : 0;       // rows inside a slab
+        constexpr int ds = planes ? dz : dy;      // along the slab axis
+        constexpr int dr = planes ? dy : 0;       // rows inside a slab
         const unsigned off = yb[kMaxDisp - dr] + static_cast<unsigned>(slot) * runb + xb[kMaxDisp - dx];
         return sb[kMaxDisp - ds] + off;
     }
@@ -377,10 +417,10 @@ struct LoadOrder {
 
 // SIGN = +1 is the pull of the forward update, SIGN = -1 the transposed
 // (adjoint) streaming.
-template <class M, int SIGN, class S>
+template <class M, int SIGN, bool FLAT, class S>
 __device__ __forceinline__ void gather(const S* __restrict__ src, const KParams& k, const Cell& cl,
                                        S (&v)[M::Q]) {
-    const SlabAddr<M, S, const char> ad(reinterpret_cast<const char*>(src), k, cl);
+    const SlabAddr<M, S, const char, FLAT, false> ad(reinterpret_cast<const char*>(src), k, cl);
     constexpr bool sorted = SIGN < 0 ? LBM_ADJ_GATHER_SORTED != 0
                                      : (M::D == 3 && LBM_FWD_GATHER_SORTED_3D != 0);
     static_for<M::Q>([&](auto I) {
@@ -393,22 +433,27 @@ __device__ __forceinline__ void gather(const S* __restrict__ src, const KParams&
 }
 
 // Writes the populations of a cell in increasing order through one running
-// 64-bit pointer (row start + population run) and the cell's 32-bit byte
-// offset inside the run.  Lanes past the end of a ragged row have x clamped
-// to 0: they compute bit-identical values for cell (0, y, z) and store them
-// there too, which keeps the stores free of per-store branches.
-template <class S>
+// 64-bit pointer (start of the row, FLAT of the row group, plus the population
+// run) and the lane's 32-bit byte offset inside the run.  Lanes that own no
+// cell compute the values of the run's last cell and store them into its
+// padding (idle lanes of a kernel that keeps them: where the last of those
+// does), which keeps the stores free of per-store branches.
+template <class S, bool FLAT, bool NT>
 struct PlaneWriter {
     char* run;
     unsigned long long runb;
     unsigned off;
-    __device__ __forceinline__ PlaneWriter(S* dst, const KParams& k, const Cell& cl, int Q)
+    __device__ __forceinline__ PlaneWriter(S* dst, const KParams& k, const Cell& cl)
         : run(reinterpret_cast<char*>(dst) +
-              static_cast<unsigned long long>(row_base(k, Q, cl.y, cl.z)) * sizeof(S)),
-          runb(static_cast<unsigned long long>(k.rs) * k.rg * sizeof(S)),
-          off(static_cast<unsigned>(cl.x) * static_cast<unsigned>(sizeof(S))) {}
+              static_cast<unsigned long long>(
+                  FLAT ? row_base(k, (__builtin_amdgcn_readfirstlane(cl.y) >> k.rg_shift)
+                                         << k.rg_shift, cl.z)
+                       : row_base(k, cl.y, cl.z)) *
+                  sizeof(S)),
+          runb(static_cast<unsigned long long>(k.ps) * sizeof(S)),
+          off(static_cast<unsigned>(cl.at) * static_cast<unsigned>(sizeof(S))) {}
     __device__ __forceinline__ void put(S val) {
-        store_pop<S>(run + off, val);
+        store_pop<S, NT>(run + off, val);
         run += runb;
     }
 };
@@ -714,14 +759,15 @@ __device__ __forceinline__ void store_held_moments(const KParams& k, const Cell&
 // POP = false (with STORE_MOM): the step's moments only, no populations are
 // relaxed or stored (the last recomputed step of a checkpoint segment,
 // whose post-collision state the next snapshot already holds).
-template <class M, class P, bool STORE_MOM, bool HOLD, bool POP = true>
+template <class M, class P, bool FLAT, bool NT, bool STORE_MOM, bool HOLD, bool POP = true>
 __global__ __launch_bounds__(row_block_limit(M::Q, P::id)) __attribute__((amdgpu_waves_per_eu(P::waves)))
 void k_step(const typename P::S* __restrict__ src, typename P::S* __restrict__ dst, KParams k,
             typename P::S* __restrict__ mom) {
     using S = typename P::S;
     constexpr int D = M::D;
     static_assert(POP || STORE_MOM, "a step stores populations, moments or both");
-    const Cell cl = row_cell<true>(k);
+    const Cell cl = row_cell<FLAT, S, true>(k);
+    if (cl.idle) return;
 
     if constexpr (HOLD) {
         const int sl = (D == 3) ? cl.z : cl.y;
@@ -729,7 +775,7 @@ void k_step(const typename P::S* __restrict__ src, typename P::S* __restrict__ d
         if (sl < k.hold_lo || sl >= L - k.hold_hi) {
             const FixedState& st = (sl < k.hold_lo) ? k.hold[0] : k.hold[1];
             if constexpr (POP) {
-                PlaneWriter<S> out_w(dst, k, cl, M::Q);
+                PlaneWriter<S, FLAT, NT> out_w(dst, k, cl);
                 feq_cell<M, P>(k, st.rho, st.U[0], st.U[1], st.U[2], st.T,
                                [&](auto, S val) { out_w.put(val); });
             }
@@ -739,10 +785,10 @@ void k_step(const typename P::S* __restrict__ src, typename P::S* __restrict__ d
     }
 
     S v[M::Q];
-    gather<M, +1>(src, k, cl, v);
+    gather<M, +1, FLAT>(src, k, cl, v);
     Macro mc;
     if constexpr (POP) {
-        PlaneWriter<S> out_w(dst, k, cl, M::Q);
+        PlaneWriter<S, FLAT, NT> out_w(dst, k, cl);
         mc = relax_cell<M, P>(k, v, [&](auto, S val) { out_w.put(val); });
     } else {
         mc = cell_macro_pinned<M, P>(k, v);
@@ -776,21 +822,21 @@ void k_step(const typename P::S* __restrict__ src, typename P::S* __restrict__ d
 // same locations instead of reading them (as k_step<HOLD> does for the
 // two-buffer step), so both schemes hold the same values.
 // STORE_MOM: also store the step's D+2 moments, as k_step<STORE_MOM> does.
-template <class M, class P, bool PUSH, bool HOLD, bool STORE_MOM>
-__global__ __launch_bounds__(row_block_limit(M::Q, P::id)) __attribute__((amdgpu_waves_per_eu(P::waves)))
+template <class M, class P, bool FLAT, bool NT, bool PUSH, bool HOLD, bool STORE_MOM>
+__global__ __launch_bounds__(row_block_limit(M::Q, P::id)) __attribute__((amdgpu_waves_per_eu(STORE_MOM || (HOLD && !FLAT) ? P::waves : P::aa_waves)))
 void k_step_aa(typename P::S* f, KParams k, typename P::S* __restrict__ mom) {
     using S = typename P::S;
     constexpr int D = M::D;
-    const Cell cl = row_cell<true>(k);
-    const SlabAddr<M, S, char> ad(reinterpret_cast<char*>(f), k, cl);
+    const Cell cl = row_cell<FLAT, S, true>(k);
+    const SlabAddr<M, S, char, FLAT, true> ad(reinterpret_cast<char*>(f), k, cl);
     const auto put = [&](auto I, S val) {
         constexpr int i = decltype(I)::value;
         constexpr int ex = M::table.e[i][0], ey = M::table.e[i][1], ez = M::table.e[i][2];
-        if (cl.active) {
+        if (!cl.idle) {
             if constexpr (PUSH)
                 store_pop<S, LBM_AA_NT_PUSH != 0>(ad.template at<i, ex, ey, ez>(), val);
             else
-                store_pop<S, LBM_AA_NT_LOCAL != 0>(ad.template at<M::table.opp[i], 0, 0, 0>(), val);
+                store_pop<S, NT>(ad.template at<M::table.opp[i], 0, 0, 0>(), val);
         }
     };
     if constexpr (HOLD) {
@@ -1075,9 +1121,9 @@ __device__ __forceinline__ R eq_pd(R c0, R c1, R c2, R s) {
 // HOLD: the post-collision values of cells on held planes are constants, so
 // their adjoint state is zero (the cells are computed like the others and
 // their output replaced, keeping every wave on the same barriers).
-template <class M, class P, bool COLLIDE, bool MARK, bool HOLD>
+template <class M, class P, bool FLAT, bool NT, bool COLLIDE, bool MARK, bool HOLD>
 __global__ __launch_bounds__(row_block_limit(M::Q, P::id))
-__attribute__((amdgpu_waves_per_eu(MARK ? (P::adj_waves < 2 ? P::adj_waves : 2) : P::adj_waves)))
+__attribute__((amdgpu_waves_per_eu(MARK || FLAT || HOLD ? (P::adj_waves < 2 ? P::adj_waves : 2) : P::adj_waves)))
 void k_adjoint(const typename P::S* __restrict__ lsrc, typename P::S* __restrict__ ldst,
                const typename P::S* __restrict__ mom, KParams k, double* __restrict__ partA,
                const typename P::S* __restrict__ mark_state, double* __restrict__ partM) {
@@ -1086,15 +1132,18 @@ void k_adjoint(const typename P::S* __restrict__ lsrc, typename P::S* __restrict
     constexpr int Q = M::Q;
     constexpr int G = M::G;
     constexpr int D = M::D;
-    const Cell cl = row_cell(k);
+    Cell cl = row_cell<FLAT, S>(k);
+    // by rows, surplus lanes repeat the store of the row's last cell: one
+    // register less than filling its line, which keeps 3 waves per SIMD
+    if constexpr (!FLAT) cl.at = cl.x;
 
     S mu[Q];
-    gather<M, -1>(lsrc, k, cl, mu);
+    gather<M, -1, FLAT>(lsrc, k, cl, mu);
 
     // MARK: mu_i B_i is accumulated where mu_i is consumed (the output loop
     // of the transposed streaming, the group sums of the collision), so
     // that the mark's loads do not extend the lifetime of mu.
-    const SlabAddr<M, S, const char> mark_at(reinterpret_cast<const char*>(mark_state), k, cl);
+    const SlabAddr<M, S, const char, FLAT, false> mark_at(reinterpret_cast<const char*>(mark_state), k, cl);
     double mk = 0.0;
     const auto mark_term = [&](auto I) {
         if constexpr (MARK) {
@@ -1107,7 +1156,7 @@ void k_adjoint(const typename P::S* __restrict__ lsrc, typename P::S* __restrict
 
     if constexpr (!COLLIDE) {
         // transposed streaming only
-        PlaneWriter<S> wt(ldst, k, cl, Q);
+        PlaneWriter<S, FLAT, NT> wt(ldst, k, cl);
         static_for<Q>([&](auto I) {
             mark_term(I);
             wt.put(mu[decltype(I)::value]);
@@ -1196,7 +1245,7 @@ void k_adjoint(const typename P::S* __restrict__ lsrc, typename P::S* __restrict
     const R ge = R(w * at * invr * (1.0 / D));
     const R gr = R(w * grho);
     const R omc = R(k.omc);
-    PlaneWriter<S> out_w(ldst, k, cl, Q);
+    PlaneWriter<S, FLAT, NT> out_w(ldst, k, cl);
     bool held = false;
     if constexpr (HOLD) {
         const int sl = (D == 3) ? cl.z : cl.y;
@@ -1288,6 +1337,18 @@ hipError_t with_initial_form(const KParams& kp, F&& f) {
     return f(std::integral_constant<int, kFormAB>{});
 }
 
+// Calls f with std::bool_constant<kp.flat>, std::bool_constant<kp.nt>.
+template <class F>
+void with_route(const KParams& kp, F&& f) {
+    if (kp.flat) {
+        if (kp.nt) f(std::true_type{}, std::true_type{});
+        else f(std::true_type{}, std::false_type{});
+    } else {
+        if (kp.nt) f(std::false_type{}, std::true_type{});
+        else f(std::false_type{}, std::false_type{});
+    }
+}
+
 }  // namespace
 
 template <class M, Prec PR>
@@ -1335,16 +1396,19 @@ hipError_t ModelKernels<M, PR>::step(const KParams& kp, const void* src, void* d
                            static_cast<S*>(mom_out));
     };
     const bool hold = kp.hold_lo + kp.hold_hi > 0;
-    if (mom_out && !dst) {
-        if (hold) go(k_step<M, P, true, true, false>);
-        else go(k_step<M, P, true, false, false>);
-    } else if (mom_out) {
-        if (hold) go(k_step<M, P, true, true>);
-        else go(k_step<M, P, true, false>);
-    } else {
-        if (hold) go(k_step<M, P, false, true>);
-        else go(k_step<M, P, false, false>);
-    }
+    with_route(kp, [&](auto F, auto T) {
+        constexpr bool flat = decltype(F)::value, nt = decltype(T)::value;
+        if (mom_out && !dst) {
+            if (hold) go(k_step<M, P, flat, nt, true, true, false>);
+            else go(k_step<M, P, flat, nt, true, false, false>);
+        } else if (mom_out) {
+            if (hold) go(k_step<M, P, flat, nt, true, true>);
+            else go(k_step<M, P, flat, nt, true, false>);
+        } else {
+            if (hold) go(k_step<M, P, flat, nt, false, true>);
+            else go(k_step<M, P, flat, nt, false, false>);
+        }
+    });
     return hipGetLastError();
 }
 
@@ -1359,17 +1423,20 @@ hipError_t ModelKernels<M, PR>::step_aa(const KParams& kp, void* f, bool push, v
                            static_cast<S*>(mom_out));
     };
     const bool hold = kp.hold_lo + kp.hold_hi > 0;
-    if (push) {
-        if (mom_out && hold) go(k_step_aa<M, P, true, true, true>);
-        else if (mom_out) go(k_step_aa<M, P, true, false, true>);
-        else if (hold) go(k_step_aa<M, P, true, true, false>);
-        else go(k_step_aa<M, P, true, false, false>);
-    } else {
-        if (mom_out && hold) go(k_step_aa<M, P, false, true, true>);
-        else if (mom_out) go(k_step_aa<M, P, false, false, true>);
-        else if (hold) go(k_step_aa<M, P, false, true, false>);
-        else go(k_step_aa<M, P, false, false, false>);
-    }
+    with_route(kp, [&](auto F, auto T) {
+        constexpr bool flat = decltype(F)::value, nt = decltype(T)::value;
+        if (push) {
+            if (mom_out && hold) go(k_step_aa<M, P, flat, false, true, true, true>);
+            else if (mom_out) go(k_step_aa<M, P, flat, false, true, false, true>);
+            else if (hold) go(k_step_aa<M, P, flat, false, true, true, false>);
+            else go(k_step_aa<M, P, flat, false, true, false, false>);
+        } else {
+            if (mom_out && hold) go(k_step_aa<M, P, flat, nt, false, true, true>);
+            else if (mom_out) go(k_step_aa<M, P, flat, nt, false, false, true>);
+            else if (hold) go(k_step_aa<M, P, flat, nt, false, true, false>);
+            else go(k_step_aa<M, P, flat, nt, false, false, false>);
+        }
+    });
     return hipGetLastError();
 }
 
@@ -1446,15 +1513,18 @@ hipError_t ModelKernels<M, PR>::adjoint_step(const KParams& kp, const void* lam_
                            static_cast<const S*>(mark_state), partM);
     };
     const bool hold = kp.hold_lo + kp.hold_hi > 0;
-    if (mom) {
-        // (the omega marks are not taken with held planes)
-        if (hold) go(k_adjoint<M, P, true, false, true>);
-        else if (mark_state) go(k_adjoint<M, P, true, true, false>);
-        else go(k_adjoint<M, P, true, false, false>);
-    } else {
-        if (mark_state) go(k_adjoint<M, P, false, true, false>);
-        else go(k_adjoint<M, P, false, false, false>);
-    }
+    with_route(kp, [&](auto F, auto T) {
+        constexpr bool flat = decltype(F)::value, nt = decltype(T)::value;
+        if (mom) {
+            // (the omega marks are not taken with held planes)
+            if (hold) go(k_adjoint<M, P, flat, nt, true, false, true>);
+            else if (mark_state) go(k_adjoint<M, P, flat, nt, true, true, false>);
+            else go(k_adjoint<M, P, flat, nt, true, false, false>);
+        } else {
+            if (mark_state) go(k_adjoint<M, P, flat, nt, false, true, false>);
+            else go(k_adjoint<M, P, flat, nt, false, false, false>);
+        }
+    });
     return hipGetLastError();
 }
 

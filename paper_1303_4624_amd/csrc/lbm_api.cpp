@@ -233,7 +233,16 @@ void fill_layout(const lbm_ctx* ctx, KParams& k) {
     // groups and 3D planes stay below 4 GiB
     k.gs = static_cast<unsigned>(ctx->Q) * static_cast<unsigned>(k.ps);
     k.zs = ctx->D == 3 ? k.gs * static_cast<unsigned>(k.gpp) : 0u;
-    k.nt = 1;
+    // Populations a step leaves in the cache are read from there by the next
+    // one: plain stores while the state (both buffers) is not much larger than
+    // the cache, non-temporal ones past that, where no line survives until it
+    // is read.  D3Q95, us per step non-temporal against plain: FP32-shifted
+    // 64^3 (199 MB) 38.9, 30.7; 64x64x96 (299 MB) 63.7, 60.2; 64x64x128 (398 MB)
+    // 80.6, 78.4; 64x64x160 (498 MB) 100.6, 101.7; 128x128x64 (797 MB) 157.9,
+    // 162.7; float64 64x64x32 (199 MB) 38.4, 31.9; in place 64x64x128 (199 MB)
+    // 64.9, 58.7 and 128x128x64 (398 MB) 129.9, 134.2; D2Q33 512^2 15.0, 12.5.
+    const long long state = static_cast<long long>(k.gs) * k.gpp * k.nz * bytes;
+    k.nt = (ctx->aa ? state : 2 * state) > lbm::kCachedState;
 }
 
 void fill_kparams(lbm_ctx* ctx) {

@@ -55,6 +55,10 @@ constexpr int kLineBytes = 128;   // a cache line
 constexpr int kRunCells = 1024;
 constexpr int kFlatCells = 384;
 
+// Bytes of populations up to which a step's stores stay in the cache (256 MB
+// shared by all XCDs); see fill_layout.
+constexpr long long kCachedState = 384LL << 20;
+
 // Threads per block of the kernels on flat groups: float64 with the
 // 4th-order sets 128 (D3Q95 200^3: 2192 us per step, 256 threads 2231 us),
 // else 256 (FP32-shifted: the same within 1 % with 128).

@@ -242,7 +242,15 @@ void fill_layout(const lbm_ctx* ctx, KParams& k) {
     // 162.7; float64 64x64x32 (199 MB) 38.4, 31.9; in place 64x64x128 (199 MB)
     // 64.9, 58.7 and 128x128x64 (398 MB) 129.9, 134.2; D2Q33 512^2 15.0, 12.5.
     const long long state = static_cast<long long>(k.gs) * k.gpp * k.nz * bytes;
-    k.nt = (ctx->aa ? state : 2 * state) > lbm::kCachedState;
+    // Between those, D3Q95 with two buffers of 16 to 40 MB: the L2s (8 of 4 MB)
+    // hold a whole step's output and write it back at the kernel's end, which
+    // non-temporal stores start earlier (FP32-shifted 32^3, 25 MB: 9.5 against
+    // 11.0 us; float64 24^3, 21 MB: 9.6, 10.7; 16^3, 6 MB: 9.3, 8.6; FP32-shifted
+    // 40^3, 49 MB: 17.9, 13.5).  The smaller sets gain nothing (D3Q15 64^3, 31
+    // MB: 7.2 against 6.6 us).
+    const long long moved = ctx->aa ? state : 2 * state;
+    k.nt = moved > lbm::kCachedState ||
+           (!ctx->aa && ctx->Q >= 95 && moved > lbm::kL2StateLo && moved <= lbm::kL2StateHi);
 }
 
 void fill_kparams(lbm_ctx* ctx) {
@@ -254,21 +262,27 @@ void fill_kparams(lbm_ctx* ctx) {
     fill_layout(ctx, k);
     k.N = ctx->N;
     const long long rows = static_cast<long long>(k.ny) * k.nz;
-    const lbm::RowLaunch rl =
-        lbm::row_launch(k.nx, rows, lbm::step_max_threads(ctx->model, ctx->prec));
+    const long long waves = k.flat ? (ctx->N + 63) / 64 : rows * ((k.nx + 63) / 64);
+    // Few waves are spread one by one over the CUs (us per step with blocks of
+    // several waves against one: D3Q95 float64 512x4x4 12.2, 9.6; 64x16x16 12.7,
+    // 9.8; FP32-shifted 28^3 10.0, 8.9; 64x48x48 21.8, 19.5; D2Q33 float64 128x4
+    // 6.1, 5.3; 400^2 16.0, 15.1; from 64^3 on the same).
+    const bool few = waves <= lbm::kFewWaves;
+    const int most = few ? 64 : lbm::step_max_threads(ctx->model, ctx->prec);
+    const lbm::RowLaunch rl = lbm::row_launch(k.nx, rows, most);
     k.chunks = rl.chunks;
     k.bx = rl.bx;
     k.rpb = 1;
     if (k.flat) {
         // the waves of a group, in blocks of equal size
-        const int waves = (k.rg * k.nx + 63) / 64;
-        const int most = lbm::flat_block_limit(ctx->Q, ctx->prec) / 64;
-        k.chunks = (waves + most - 1) / most;
-        k.bx = (waves + k.chunks - 1) / k.chunks * 64;
+        const int group = (k.rg * k.nx + 63) / 64;
+        const int per = few ? 1 : lbm::flat_block_limit(ctx->Q, ctx->prec) / 64;
+        k.chunks = (group + per - 1) / per;
+        k.bx = (group + k.chunks - 1) / k.chunks * 64;
     } else if (lbm::kPackRows && k.nx % 64 == 0) {
         // whole rows per block: waves stay inside one row (nx % 64 = 0) and
         // no block is partly empty (rpb divides the row count)
-        const int maxb = std::min(lbm::step_max_threads(ctx->model, ctx->prec), lbm::kPackMaxBlock);
+        const int maxb = std::min(most, lbm::kPackMaxBlock);
         while (k.nx * k.rpb * 2 <= maxb && rows % (k.rpb * 2) == 0) k.rpb *= 2;
         if (k.rpb > 1) k.bx = k.nx * k.rpb;   // else: the row launch above (chunks >= 1)
     }

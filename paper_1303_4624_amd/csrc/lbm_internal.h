@@ -58,6 +58,11 @@ constexpr int kFlatCells = 384;
 // Bytes of populations up to which a step's stores stay in the cache (256 MB
 // shared by all XCDs); see fill_layout.
 constexpr long long kCachedState = 384LL << 20;
+constexpr long long kL2StateLo = 16LL << 20;
+constexpr long long kL2StateHi = 40LL << 20;
+
+// Grids of at most this many waves take blocks of one wave.
+constexpr int kFewWaves = 4096;
 
 // Threads per block of the kernels on flat groups: float64 with the
 // 4th-order sets 128 (D3Q95 200^3: 2192 us per step, 256 threads 2231 us),

@@ -253,6 +253,25 @@ void fill_layout(const lbm_ctx* ctx, KParams& k) {
            (!ctx->aa && ctx->Q >= 95 && moved > lbm::kL2StateLo && moved <= lbm::kL2StateHi);
 }
 
+lbm::FastDiv fast_div(int d) {
+    lbm::FastDiv f;
+    f.shift = 31;
+    while ((1LL << (f.shift - 31)) < d) ++f.shift;
+    f.mul = static_cast<unsigned>((1ULL << f.shift) / static_cast<unsigned>(d) + 1);
+    return f;
+}
+
+// Divisions of the lane-to-cell mapping.
+void set_divisors(KParams& k) {
+    k.by_nx = fast_div(k.nx);
+    k.by_ny = fast_div(k.ny);
+    k.by_gpp = fast_div(k.gpp);
+    k.by_chunks = fast_div(k.chunks);
+    k.inv_nx = 65536u / static_cast<unsigned>(k.nx) + 1;
+    k.inv_ny = 65536u / static_cast<unsigned>(k.ny) + 1;
+    k.inv_nz = 65536u / static_cast<unsigned>(k.nz) + 1;
+}
+
 void fill_kparams(lbm_ctx* ctx) {
     KParams& k = ctx->kp;
     if (!ctx->initialized) k.form = initial_form(ctx);
@@ -286,6 +305,7 @@ void fill_kparams(lbm_ctx* ctx) {
         while (k.nx * k.rpb * 2 <= maxb && rows % (k.rpb * 2) == 0) k.rpb *= 2;
         if (k.rpb > 1) k.bx = k.nx * k.rpb;   // else: the row launch above (chunks >= 1)
     }
+    set_divisors(k);
     k.xcd_cyclic = ctx->mapping ? cyclic_chunk(k, ctx->D) : 0;
     k.omega = ctx->omega;
     k.omc = 1.0 - ctx->omega;

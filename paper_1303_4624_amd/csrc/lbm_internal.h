@@ -100,6 +100,14 @@ constexpr int kFormAB = 0;        // two buffers: run i of cell c
 constexpr int kFormSwapped = 1;   // in place, after an even number of steps: run opp(i) of c
 constexpr int kFormPushed = 2;    // in place, after an odd number of steps: run i of c + e_i
 
+// Division of a non-negative 32-bit number by a constant: n * mul >> shift,
+// with shift = 31 + ceil(log2 d) and mul = floor(2^shift / d) + 1 < 2^32,
+// exact for n < 2^31 (the rounding error n / 2^shift stays below 1/d).
+struct FastDiv {
+    unsigned mul;
+    int shift;
+};
+
 // Per-context constants, passed to every kernel by value.  Per group only
 // the weight W_g and X_g = |e_g|^2 / T0 are arguments (argument values live
 // in scalar registers; the kernels form every other coefficient of the
@@ -121,6 +129,8 @@ struct KParams {
     int chunks;               // blocks per grid row (x direction); flat: per row group
     int rpb;                  // grid rows per block (> 1 only with chunks = 1, nx % 64 = 0)
     int bx;                   // threads per block (multiple of 64)
+    FastDiv by_nx, by_ny, by_gpp, by_chunks;
+    unsigned inv_nx, inv_ny, inv_nz;   // 65536 / n + 1 (axes of at most kMaxDisp cells)
     int xcd_cyclic;           // > 0: the forward steps hand the 8 XCDs chunks of this
                               // many blocks in turn; 0: a contiguous range each
     long long N;              // cells

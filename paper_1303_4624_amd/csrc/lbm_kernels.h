@@ -152,6 +152,35 @@ __device__ __forceinline__ int wrap_idx(int v, int n) {
     return v < 0 ? v + n : v;
 }
 
+// Entries v - d, d = -kMaxDisp .. kMaxDisp, modulo n for v in [0, n): one
+// uniform branch for all of them and no division (an axis shorter than a
+// displacement wraps more than once; inv = 65536 / n + 1 there).  The address
+// set-up is on the critical path of a small grid's step.
+__device__ __forceinline__ void wrap_all(int v, int n, unsigned inv, int (&o)[kW]) {
+    const unsigned un = static_cast<unsigned>(n);
+    if (n > kMaxDisp) {
+        static_for<kW>([&](auto DI) {
+            constexpr int d = decltype(DI)::value - kMaxDisp;
+            unsigned u = static_cast<unsigned>(v - d);   // wraps past 2^31 below 0
+            u = min(u, u + un);
+            u = min(u, u - un);
+            o[d + kMaxDisp] = static_cast<int>(u);
+        });
+    } else {
+        static_for<kW>([&](auto DI) {
+            constexpr int d = decltype(DI)::value - kMaxDisp;
+            const unsigned u = static_cast<unsigned>(v - d) + kMaxDisp * un;
+            o[d + kMaxDisp] = static_cast<int>(u - ((u * inv) >> 16) * un);
+        });
+    }
+}
+
+// n / d for n < 2^31.
+__device__ __forceinline__ int div_by(int n, const FastDiv& d) {
+    return static_cast<int>(
+        (static_cast<unsigned long long>(static_cast<unsigned>(n)) * d.mul) >> d.shift);
+}
+
 struct Cell {
     int x, y, z;        // the cell; lanes that own none take the last cell of their run
     int at;             // element of the population run the lane stores to
@@ -273,8 +302,8 @@ __device__ __forceinline__ Cell row_cell(const KParams& k) {
 #endif
     Cell cl;
     if constexpr (FLAT) {
-        const int gi = b / k.chunks;
-        const int z = gi / k.gpp, y0 = (gi - z * k.gpp) << k.rg_shift;
+        const int gi = div_by(b, k.by_chunks);
+        const int z = div_by(gi, k.by_gpp), y0 = (gi - z * k.gpp) << k.rg_shift;
         const int cells = (k.ny - y0 < k.rg ? k.ny - y0 : k.rg) * k.nx;
         const int j = (b - gi * k.chunks) * k.bx + static_cast<int>(threadIdx.x);
         constexpr int line = kLineBytes / static_cast<int>(sizeof(S));
@@ -283,10 +312,10 @@ __device__ __forceinline__ Cell row_cell(const KParams& k) {
         cl.active = j < cells;
         cl.idle = j >= lim;
         cl.at = cl.idle ? lim - 1 : j;
-        const unsigned jc = static_cast<unsigned>(cl.active ? j : cells - 1);
-        const unsigned r = jc / static_cast<unsigned>(k.nx);
-        cl.x = static_cast<int>(jc - r * static_cast<unsigned>(k.nx));
-        cl.y = y0 + static_cast<int>(r);
+        const int jc = cl.active ? j : cells - 1;
+        const int r = div_by(jc, k.by_nx);
+        cl.x = jc - r * k.nx;
+        cl.y = y0 + r;
         cl.z = z;
         cl.c = (static_cast<long long>(z) * k.ny + y0) * k.nx + jc;
     } else {
@@ -298,16 +327,15 @@ __device__ __forceinline__ Cell row_cell(const KParams& k) {
             row = b * k.rpb + sub;
             x = static_cast<int>(threadIdx.x) - sub * k.nx;
         } else {
-            const int chunk = b % k.chunks;
-            row = b / k.chunks;
-            x = chunk * k.bx + static_cast<int>(threadIdx.x);
+            row = div_by(b, k.by_chunks);
+            x = (b - row * k.chunks) * k.bx + static_cast<int>(threadIdx.x);
         }
         cl.active = x < k.nx;
         cl.idle = x >= k.lim;
         cl.x = cl.active ? x : k.nx - 1;
         cl.at = cl.idle ? k.lim - 1 : x;
-        cl.y = row % k.ny;
-        cl.z = row / k.ny;
+        cl.z = div_by(row, k.by_ny);
+        cl.y = row - cl.z * k.ny;
         cl.c = static_cast<long long>(row) * k.nx + cl.x;
     }
     return cl;
@@ -331,25 +359,35 @@ struct SlabAddr {
         const unsigned rsb = static_cast<unsigned>(k.rs) * w;
         runb = static_cast<unsigned>(k.ps) * w;
         const bool pad = OWN && !cl.active;
+        int xs[kW], ys[kW], zs[kW];   // entry d: the cell at -d
+        wrap_all(cl.x, k.nx, k.inv_nx, xs);
+        wrap_all(cl.y, k.ny, k.inv_ny, ys);
+        if constexpr (M::D == 3) wrap_all(cl.z, k.nz, k.inv_nz, zs);
         static_for<kW>([&](auto DI) {
-            constexpr int d = decltype(DI)::value - kMaxDisp;   // table entry d: cell at -d
-            xb[d + kMaxDisp] = static_cast<unsigned>(pad ? cl.at : wrap_idx(cl.x - d, k.nx)) * w;
-            const int yr = FLAT && pad ? cl.y : wrap_idx(cl.y - d, k.ny);
+            constexpr int d = decltype(DI)::value;
+            xb[d] = static_cast<unsigned>(pad ? cl.at : xs[d]) * w;
+            const int yr = FLAT && pad ? cl.y : ys[d];
             const int gy = yr >> k.rg_shift;
             const int ry = FLAT && pad ? 0 : yr - (gy << k.rg_shift);
             if constexpr (planes) {
-                yb[d + kMaxDisp] =
-                    static_cast<unsigned>(gy) * (k.gs * w) + static_cast<unsigned>(ry) * rsb;
-                sb[d + kMaxDisp] =
-                    base + static_cast<unsigned long long>(wrap_idx(cl.z - d, k.nz)) * (k.zs * w);
+                yb[d] = static_cast<unsigned>(gy) * (k.gs * w) + static_cast<unsigned>(ry) * rsb;
+                if constexpr (M::D == 3)
+                    sb[d] = base + static_cast<unsigned long long>(zs[d]) * (k.zs * w);
+                else
+                    sb[d] = base;
             } else {
-                yb[d + kMaxDisp] = 0u;
-                sb[d + kMaxDisp] = base + static_cast<unsigned long long>(gy) * (k.gs * w) +
-                                   static_cast<unsigned long long>(ry) * rsb;
+                yb[d] = 0u;
+                sb[d] = base + static_cast<unsigned long long>(gy) * (k.gs * w) +
+                        static_cast<unsigned long long>(ry) * rsb;
             }
         });
     }
-template <int slot, int dx, int dy, int dz>
+    // Ends the compiler's view of the offsets: a kernel that stores where it
+    // has loaded forms each address again instead of holding Q of them.
+    __device__ __forceinline__ void forget() {
+        static_for<kW>([&](auto DI) { asm volatile("" : "+v"(xb[decltype(DI)::value])); });
+    }
+    template <int slot, int dx, int dy, int dz>
     __device__ __forceinline__ B* at() const {
         constexpr int ds = planes ? dz : dy;      // along the slab axis
         constexpr int dr = planes ? dy : 0;       // rows inside a slab
@@ -828,7 +866,7 @@ void k_step_aa(typename P::S* f, KParams k, typename P::S* __restrict__ mom) {
     using S = typename P::S;
     constexpr int D = M::D;
     const Cell cl = row_cell<FLAT, S, true>(k);
-    const SlabAddr<M, S, char, FLAT, true> ad(reinterpret_cast<char*>(f), k, cl);
+    SlabAddr<M, S, char, FLAT, true> ad(reinterpret_cast<char*>(f), k, cl);
     const auto put = [&](auto I, S val) {
         constexpr int i = decltype(I)::value;
         constexpr int ex = M::table.e[i][0], ey = M::table.e[i][1], ez = M::table.e[i][2];
@@ -858,6 +896,7 @@ void k_step_aa(typename P::S* f, KParams k, typename P::S* __restrict__ mom) {
         else
             v[i] = load_pop<S>(ad.template at<i, 0, 0, 0>());
     });
+    ad.forget();
     const Macro mc = cell_macro_pinned<M, P>(k, v);
     relax_with<M, P>(k, v, mc, put);
     if constexpr (STORE_MOM) {

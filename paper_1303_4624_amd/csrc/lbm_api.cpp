@@ -272,6 +272,56 @@ void set_divisors(KParams& k) {
     k.inv_nz = 65536u / static_cast<unsigned>(k.nz) + 1;
 }
 
+// Strips of a narrow 2D grid (k_steps_strip): steps per launch and strip width
+// by the time they are expected to take.  A launch costs about `fixed` us
+// beside its steps, a step of a block `wave` us while it has one wave per SIMD
+// and `two` with two (measured: D2Q33 float64 128x4, 7 steps of strips of 4:
+// 2.9 us per step, 5x1500 in strips of 16 3.4, 300x12 5 steps 3.7, 11x800 held 5
+// steps 4.0; FP32-shifted 128x4 2.5, 11x800 3.6).  Single steps take about
+// `single` (the same grids: 4.2-5.0, 4.9, 3.9, 5.0; 4.3, 5.1), so strips are
+// taken where they promise a tenth less: up to about 16 cells across.  All
+// blocks run at once (one per CU, the strip's LDS).
+void strip_plan(lbm_ctx* ctx) {
+    KParams& k = ctx->kp;
+    lbm::StripParams& sp = k.strip;
+    k.steps = 1;
+    sp = lbm::StripParams{};
+    sp.steps = 1;
+    if (ctx->D != 2 || ctx->aa) return;
+    const bool f64 = ctx->prec == Prec::F64;
+    const double fixed = f64 ? 1.6 : 1.4, wave = f64 ? 2.6 : 2.2, two = f64 ? 4.2 : 3.4,
+                 single = f64 ? 4.4 : 4.2;
+    const int reach = lbm::model_reach(ctx->model);
+    sp.along_y = k.ny >= k.nx;
+    sp.n = sp.along_y ? k.ny : k.nx;
+    sp.s = sp.along_y ? k.nx : k.ny;
+    if (sp.s > lbm::kStripCells) return;
+    double best = 0.9 * single;
+    for (int steps : {7, 5, 3, 2}) {
+        for (int w = reach; w <= lbm::kStripCells; w += reach) {
+            const int margin = reach * (steps - 1);
+            const bool whole = w + 2 * margin >= sp.n;
+            const int len = whole ? sp.n : w + 2 * margin;
+            if (static_cast<long long>(len) * sp.s > lbm::kStripCells) break;
+            const int blocks = whole ? 1 : (sp.n + w - 1) / w;
+            if (blocks > lbm::kCUs) continue;
+            double us = fixed;
+            for (int t = 0; t < steps; ++t)
+                us += ((whole ? len : len - 2 * reach * t) * sp.s > 256) ? two : wave;
+            if (us / steps < best) {
+                best = us / steps;
+                sp.steps = steps;
+                sp.w = whole ? sp.n : w;
+                sp.threads = (len * sp.s + 63) / 64 * 64;
+            }
+            if (whole) break;
+        }
+    }
+    sp.by_s = fast_div(sp.s);
+    sp.inv_s = 65536u / static_cast<unsigned>(sp.s) + 1;
+    sp.inv_n = 65536u / static_cast<unsigned>(sp.n) + 1;
+}
+
 void fill_kparams(lbm_ctx* ctx) {
     KParams& k = ctx->kp;
     if (!ctx->initialized) k.form = initial_form(ctx);
@@ -306,6 +356,7 @@ void fill_kparams(lbm_ctx* ctx) {
         if (k.rpb > 1) k.bx = k.nx * k.rpb;   // else: the row launch above (chunks >= 1)
     }
     set_divisors(k);
+    strip_plan(ctx);
     k.xcd_cyclic = ctx->mapping ? cyclic_chunk(k, ctx->D) : 0;
     k.omega = ctx->omega;
     k.omc = 1.0 - ctx->omega;
@@ -533,6 +584,25 @@ hipError_t launch_one_step(lbm_ctx* ctx) {
     return e;
 }
 
+// n >= 3 steps in strips (kp.strip.steps a launch at most).  Every launch moves
+// the state to the other buffer; their number has the parity of n, so that the
+// state lies where n single steps leave it (a caller may replay an even number
+// of captured steps).
+int launch_strips(lbm_ctx* ctx, int n) {
+    const int most = ctx->kp.strip.steps;
+    int launches = (n + most - 1) / most;
+    if ((launches ^ n) & 1) ++launches;
+    for (int left = n; left > 0; --launches) {
+        const int now = (left + launches - 1) / launches;   // as even as they come
+        ctx->kp.steps = now;
+        const hipError_t e = launch_one_step(ctx);
+        ctx->kp.steps = 1;
+        if (e != hipSuccess) return fail_hip(ctx, e, "step kernel");
+        left -= now;
+    }
+    return LBM_OK;
+}
+
 // Captures graph_steps steps from the current launch state.  The state
 // after an even number of steps equals the one before, so the graph can be
 // replayed as long as that state is current.
@@ -665,6 +735,10 @@ LBM_API int lbm_step(lbm_ctx* ctx, int n) {
             if (e != hipSuccess) return fail_hip(ctx, e, "hipGraphLaunch");
             left -= ctx->graph_steps;
         }
+    }
+    if (ctx->kp.strip.steps > 1 && left > 2) {
+        if ((rc = launch_strips(ctx, left)) != LBM_OK) return rc;
+        left = 0;
     }
     for (; left > 0; --left) {
         hipError_t e = launch_one_step(ctx);

@@ -17,6 +17,8 @@ int model_groups(ModelId m);
 int model_group_of(ModelId m, int i);
 int model_e(ModelId m, int i, int k);
 int model_e2(ModelId m, int g);
+// Largest |component| of a model's velocities.
+int model_reach(ModelId m);
 // Order of accuracy m of a compiled model (its equilibrium has order N = m).
 int model_order(ModelId m);
 // True if e (int32[Q][D]) is the canonical velocity list of the model.

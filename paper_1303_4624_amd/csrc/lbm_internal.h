@@ -108,6 +108,19 @@ struct FastDiv {
     int shift;
 };
 
+// Several steps of a narrow 2D grid per launch (k_steps_strip): strips of w
+// cells of the long axis (n cells; y if along_y), s cells across.
+constexpr int kStripCells = 512;   // cells of a strip with its margins, one per thread
+constexpr int kCUs = 256;
+struct StripParams {
+    int steps;     // at most, 1: no strips
+    int w, n, s;
+    int along_y;
+    int threads;
+    FastDiv by_s;
+    unsigned inv_s, inv_n;
+};
+
 // Per-context constants, passed to every kernel by value.  Per group only
 // the weight W_g and X_g = |e_g|^2 / T0 are arguments (argument values live
 // in scalar registers; the kernels form every other coefficient of the
@@ -144,6 +157,8 @@ struct KParams {
     double X[kMaxG];          // |e_g|^2 / T0 per group
     int hold_lo, hold_hi;     // planes of the slowest axis held at f^eq(hold[0] / hold[1])
     FixedState hold[2];
+    int steps;                // steps of this launch (> 1: in strips)
+    StripParams strip;
 };
 
 // Launch geometry of the row-blocked kernels: one grid row (fixed y, z) is
@@ -170,7 +185,8 @@ hipError_t launch_set_pop(ModelId m, Prec p, const KParams& kp, const double* fi
                           hipStream_t s);
 hipError_t launch_get_pop(ModelId m, Prec p, const KParams& kp, const void* f, double* fout,
                           hipStream_t s);
-// One update step from src into dst.  mom_out != nullptr: also store the
+// One update step from src into dst; kp.steps > 1 (2D, no moments): that many,
+// in the strips of kp.strip.  mom_out != nullptr: also store the
 // step's D+2 moments (recomputation for the adjoint).  dst == nullptr (with
 // mom_out): gather and store the moments only, no populations (the last
 // recomputed step of a segment, whose state the next checkpoint holds).

@@ -910,6 +910,105 @@ void k_step_aa(typename P::S* f, KParams k, typename P::S* __restrict__ mom) {
     }
 }
 
+// Several forward steps of a narrow 2D grid in one launch (two buffers).  A
+// block advances a strip of sp.w cells of the long axis, over the whole short
+// one, k.steps steps: the first step gathers from src, the intermediate
+// states stay in LDS, the last step stores to dst.  The strip starts with a
+// margin of emax*(steps - 1) cells on either side and loses emax of it at each
+// step, so blocks exchange nothing; sp.w = sp.n needs no margin.
+// Such grids are bound by the launch, the first load and the last store of a
+// step, not by arithmetic: recomputing the margins costs less than a launch
+// (strip_plan in lbm_api.cpp).  One cell per thread; LDS holds population i of
+// strip cell (l, q), l along the long axis, at i*kStripCells + l*sp.s + q.
+// The arithmetic of a cell is k_step's, so the results are the same bits.
+template <class M, class P, bool HOLD>
+__global__ __launch_bounds__(kStripCells) void k_steps_strip(
+    const typename P::S* __restrict__ src, typename P::S* __restrict__ dst, KParams k) {
+    using S = typename P::S;
+    const StripParams& sp = k.strip;
+    const int steps = k.steps;
+    constexpr int Q = M::Q, E = M::table.emax;
+    static_assert(M::D == 2 && E <= kMaxDisp, "2D sets");
+    __shared__ S lds[Q * kStripCells];
+    const int tid = static_cast<int>(threadIdx.x);
+    const bool whole = sp.w >= sp.n;
+    const int margin = whole ? 0 : E * (steps - 1);
+    const int len = sp.w + 2 * margin;
+    const int origin = static_cast<int>(blockIdx.x) * sp.w - margin;
+#pragma unroll 1
+    for (int t = 0; t < steps; ++t) {
+        const int lo = whole ? 0 : E * t;
+        const bool active = tid < (len - 2 * lo) * sp.s;
+        const int j = lo * sp.s + (active ? tid : 0);
+        const int l = div_by(j, sp.by_s);
+        const int q = j - l * sp.s;
+        int g = origin + l;                    // place on the long axis
+        const bool own = g < sp.n;             // false: past the last strip's end
+        g += g < 0 ? sp.n : 0;
+        g -= g >= sp.n ? sp.n : 0;
+        Cell cl;
+        cl.x = sp.along_y ? q : g;
+        cl.y = sp.along_y ? g : q;
+        cl.z = 0;
+        cl.active = true;
+        S v[Q];
+        if (t == 0) {
+            if (active) gather<M, +1, true>(src, k, cl, v);
+        } else {
+            int lq[2][kW];
+            wrap_all(q, sp.s, sp.inv_s, lq[1]);
+            if (whole) {
+                wrap_all(l, sp.n, sp.inv_n, lq[0]);
+            } else {
+                static_for<kW>([&](auto DI) {
+                    constexpr int d = decltype(DI)::value;
+                    lq[0][d] = l - (d - kMaxDisp);
+                });
+            }
+            static_for<kW>([&](auto DI) { lq[0][decltype(DI)::value] *= sp.s; });
+            const auto pull = [&](auto A) {    // A: index of the component along the long axis
+                constexpr int a = decltype(A)::value;
+                static_for<Q>([&](auto I) {
+                    constexpr int i = decltype(I)::value;
+                    constexpr int el = M::table.e[i][a], eq = M::table.e[i][1 - a];
+                    v[i] = lds[i * kStripCells + lq[0][kMaxDisp + el] + lq[1][kMaxDisp + eq]];
+                });
+            };
+            if (active) {
+                if (sp.along_y) pull(std::integral_constant<int, 1>{});
+                else pull(std::integral_constant<int, 0>{});
+            }
+            __syncthreads();                   // every read is done before the writes below
+        }
+        S out[Q];
+        const auto keep = [&](auto I, S val) { out[decltype(I)::value] = val; };
+        if (active) {
+            bool held = false;
+            if constexpr (HOLD) {
+                held = cl.y < k.hold_lo || cl.y >= k.ny - k.hold_hi;
+                if (held) {
+                    const FixedState& st = (cl.y < k.hold_lo) ? k.hold[0] : k.hold[1];
+                    feq_cell<M, P>(k, st.rho, st.U[0], st.U[1], st.U[2], st.T, keep);
+                }
+            }
+            if (!held) relax_cell<M, P>(k, v, keep);
+            if (t + 1 < steps) {
+                static_for<Q>([&](auto I) {
+                    constexpr int i = decltype(I)::value;
+                    lds[i * kStripCells + j] = out[i];
+                });
+            } else if (own) {
+                const SlabAddr<M, S, char, true, false> ad(reinterpret_cast<char*>(dst), k, cl);
+                static_for<Q>([&](auto I) {
+                    constexpr int i = decltype(I)::value;
+                    store_pop<S, false>(ad.template at<i, 0, 0, 0>(), out[i]);
+                });
+            }
+        }
+        __syncthreads();                       // the next step reads what was written
+    }
+}
+
 // ---------------------------------------------------------------------------
 // f = f^eq(rho, U, T) from float64 fields.
 template <class M, class P, int FORM>
@@ -1428,13 +1527,29 @@ hipError_t ModelKernels<M, PR>::step(const KParams& kp, const void* src, void* d
                                      void* mom_out, hipStream_t s) {
     using P = typename PrecOf<PR>::type;
     using S = typename P::S;
+    const bool hold = kp.hold_lo + kp.hold_hi > 0;
+    if (kp.steps > 1) {
+        if constexpr (M::D == 2) {
+            if (!dst || mom_out) return hipErrorInvalidValue;
+            const StripParams& sp = kp.strip;
+            const dim3 strips(static_cast<unsigned>((sp.n + sp.w - 1) / sp.w));
+            const auto go = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, strips, dim3(sp.threads), 0, s,
+                                   static_cast<const S*>(src), static_cast<S*>(dst), kp);
+            };
+            if (hold) go(k_steps_strip<M, P, true>);
+            else go(k_steps_strip<M, P, false>);
+            return hipGetLastError();
+        } else {
+            return hipErrorInvalidValue;
+        }
+    }
     const dim3 grid(static_cast<unsigned>(step_blocks(M::id, PR, kp)));
     const auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, dim3(kp.bx), 0, s,
                            static_cast<const S*>(src), static_cast<S*>(dst), kp,
                            static_cast<S*>(mom_out));
     };
-    const bool hold = kp.hold_lo + kp.hold_hi > 0;
     with_route(kp, [&](auto F, auto T) {
         constexpr bool flat = decltype(F)::value, nt = decltype(T)::value;
         if (mom_out && !dst) {

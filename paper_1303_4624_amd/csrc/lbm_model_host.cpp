@@ -314,6 +314,13 @@ int model_group_of(ModelId m, int i) { return view(m).group[i]; }
 int model_e(ModelId m, int i, int k) { return view(m).e[i][k]; }
 int model_e2(ModelId m, int g) { return view(m).e2[g]; }
 int model_order(ModelId m) { return view(m).m; }
+int model_reach(ModelId m) {
+    const ModelView v = view(m);
+    int r = 0;
+    for (int i = 0; i < v.Q; ++i)
+        for (int k = 0; k < v.D; ++k) r = std::max(r, std::abs(v.e[i][k]));
+    return r;
+}
 
 bool model_matches(ModelId m, const int32_t* e) {
     const ModelView v = view(m);

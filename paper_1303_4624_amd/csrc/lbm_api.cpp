@@ -272,6 +272,82 @@ void set_divisors(KParams& k) {
     k.inv_nz = 65536u / static_cast<unsigned>(k.nz) + 1;
 }
 
+// Kernels that share a block size.
+enum BlockUse { kSteps, kStepsInPlace, kAdjoint };
+
+// Blocks of the kernels that advance cells: their size, and how many a CU holds
+// at once (k.resident).
+//
+// Few waves are spread one by one over the CUs (us per step with blocks of
+// several waves against one: D3Q95 float64 512x4x4 12.2, 9.6; 64x16x16 12.7,
+// 9.8; FP32-shifted 28^3 10.0, 8.9; 64x48x48 21.8, 19.5; D2Q33 float64 128x4 6.1,
+// 5.3; 400^2 16.0, 15.1; from 64^3 on the same).
+//
+// States past the cache (k.nt) are bound by HBM, whose rate falls as more waves
+// read and write their own places in it at once: a CU is held to 4 to 8 waves,
+// in the fewest blocks.  us per step, unlimited against held, on the same
+// buffers: D3Q95 FP32-shifted one block of 512 or a 384-cell row (128^3 292,
+// 281; 256^3 2258, 2182; 384^3 7770, 7503; 200^3 1144, 1105), float64 one of 256
+// (256^3 4440, 4285; 150^3 937, 898); D2Q33 FP32-shifted one of 512 (2393x3579
+// 403, 388; 8192^2 2914, 2867), float64 two of 256 (814, 788); D3Q19
+// FP32-shifted two of 256 (256^3 438, 416), float64 the same (889, 856).
+// In place the writes hit lines other blocks read: D3Q95 FP32-shifted two
+// blocks of 128 from 1 GB (256^3 2411, 2323; 384^3 8260, 8010; 170x145x141 525,
+// 506), below that blocks of 256 alone (128^3 298, 286, held 289; 128x128x90
+// 192, 191, held 203); float64 one of 256 on flat groups (200^3 2439, 2322),
+// none by rows (256^3 4786, held 4829); the smaller sets two of 256 (D2Q33
+// 2000^2 204, 191, float64 398, 377; D3Q19 256^3 471, 446).  The cache prefers
+// many waves (64^3 FP32-shifted 30, held 49), and so does the adjoint's mix of
+// arithmetic and loads (128^3, 40 steps: 18.5 ms with and without).
+void set_blocks(const lbm_ctx* ctx, KParams& k, BlockUse use) {
+    const long long rows = static_cast<long long>(k.ny) * k.nz;
+    const long long waves = k.flat ? (ctx->N + 63) / 64 : rows * ((k.nx + 63) / 64);
+    const bool few = waves <= lbm::kFewWaves, f64 = ctx->prec == Prec::F64;
+    int most = lbm::step_max_threads(ctx->model, ctx->prec);
+    int flat_most = lbm::flat_block_limit(ctx->Q, ctx->prec);
+    int pack_most = use == kAdjoint ? lbm::kPackAdjMaxBlock : lbm::kPackMaxBlock;
+    k.resident = 0;
+    if (few) {
+        most = flat_most = pack_most = 64;
+    } else if (k.nt && use != kAdjoint) {
+        if (ctx->Q >= 95 && use == kSteps) {
+            flat_most = most;
+            k.resident = 1;
+        } else if (ctx->Q >= 95 && !f64) {
+            k.resident = pop_bytes(ctx) >= (size_t{1} << 30) ? 2 : 0;
+            most = flat_most = k.resident ? 128 : 256;
+        } else if (ctx->Q >= 95) {
+            flat_most = most;
+            k.resident = k.flat ? 1 : 0;
+        } else if (ctx->Q >= 33 && use == kSteps && !f64) {
+            flat_most = most;
+            k.resident = 1;
+        } else {
+            most = flat_most = 256;
+            k.resident = 2;
+        }
+    }
+    k.rpb = 1;
+    if (k.flat) {
+        // the waves of a group, in blocks of equal size
+        const int group = (k.rg * k.nx + 63) / 64;
+        k.chunks = (group + flat_most / 64 - 1) / (flat_most / 64);
+        k.bx = (group + k.chunks - 1) / k.chunks * 64;
+    } else {
+        const lbm::RowLaunch rl = lbm::row_launch(k.nx, rows, most);
+        k.chunks = rl.chunks;
+        k.bx = rl.bx;
+        if (lbm::kPackRows && k.nx % 64 == 0) {
+            // whole rows per block: waves stay inside one row (nx % 64 = 0) and
+            // no block is partly empty (rpb divides the row count)
+            const int maxb = std::min(most, pack_most);
+            while (k.nx * k.rpb * 2 <= maxb && rows % (k.rpb * 2) == 0) k.rpb *= 2;
+            if (k.rpb > 1) k.bx = k.nx * k.rpb;   // else: the row launch above (chunks >= 1)
+        }
+    }
+    set_divisors(k);
+}
+
 // Strips of a narrow 2D grid (k_steps_strip): steps per launch and strip width
 // by the time they are expected to take.  A launch costs about `fixed` us
 // beside its steps, a step of a block `wave` us while it has one wave per SIMD
@@ -330,32 +406,7 @@ void fill_kparams(lbm_ctx* ctx) {
     k.nz = ctx->D == 3 ? static_cast<int>(ctx->extent[2]) : 1;
     fill_layout(ctx, k);
     k.N = ctx->N;
-    const long long rows = static_cast<long long>(k.ny) * k.nz;
-    const long long waves = k.flat ? (ctx->N + 63) / 64 : rows * ((k.nx + 63) / 64);
-    // Few waves are spread one by one over the CUs (us per step with blocks of
-    // several waves against one: D3Q95 float64 512x4x4 12.2, 9.6; 64x16x16 12.7,
-    // 9.8; FP32-shifted 28^3 10.0, 8.9; 64x48x48 21.8, 19.5; D2Q33 float64 128x4
-    // 6.1, 5.3; 400^2 16.0, 15.1; from 64^3 on the same).
-    const bool few = waves <= lbm::kFewWaves;
-    const int most = few ? 64 : lbm::step_max_threads(ctx->model, ctx->prec);
-    const lbm::RowLaunch rl = lbm::row_launch(k.nx, rows, most);
-    k.chunks = rl.chunks;
-    k.bx = rl.bx;
-    k.rpb = 1;
-    if (k.flat) {
-        // the waves of a group, in blocks of equal size
-        const int group = (k.rg * k.nx + 63) / 64;
-        const int per = few ? 1 : lbm::flat_block_limit(ctx->Q, ctx->prec) / 64;
-        k.chunks = (group + per - 1) / per;
-        k.bx = (group + k.chunks - 1) / k.chunks * 64;
-    } else if (lbm::kPackRows && k.nx % 64 == 0) {
-        // whole rows per block: waves stay inside one row (nx % 64 = 0) and
-        // no block is partly empty (rpb divides the row count)
-        const int maxb = std::min(most, lbm::kPackMaxBlock);
-        while (k.nx * k.rpb * 2 <= maxb && rows % (k.rpb * 2) == 0) k.rpb *= 2;
-        if (k.rpb > 1) k.bx = k.nx * k.rpb;   // else: the row launch above (chunks >= 1)
-    }
-    set_divisors(k);
+    set_blocks(ctx, k, ctx->aa ? kStepsInPlace : kSteps);
     strip_plan(ctx);
     k.xcd_cyclic = ctx->mapping ? cyclic_chunk(k, ctx->D) : 0;
     k.omega = ctx->omega;
@@ -1106,16 +1157,13 @@ LBM_API int lbm_restore_checkpoint(lbm_ctx* ctx, int n, int k, int keep, const v
 
 namespace {
 
-// Launch parameters of the adjoint (its recomputation included): the
-// two-buffer form whatever scheme the forward run used, and packed-row
-// blocks of at most kPackAdjMaxBlock threads.
-KParams adjoint_params(const lbm_ctx* ctx) {
+// Launch parameters of the adjoint's kernels: the two-buffer form whatever
+// scheme the forward run used.
+KParams adjoint_params(const lbm_ctx* ctx, BlockUse use) {
     KParams k = ctx->kp;
     k.form = lbm::kFormAB;
-    if (k.rpb > 1) {
-        while (k.rpb > 1 && k.nx * k.rpb > lbm::kPackAdjMaxBlock) k.rpb /= 2;
-        k.bx = k.nx * k.rpb;   // rows of nx = 64 j cells: one chunk per row
-    }
+    set_blocks(ctx, k, use);
+    k.xcd_cyclic = ctx->mapping ? cyclic_chunk(k, ctx->D) : 0;
     return k;
 }
 
@@ -1134,7 +1182,7 @@ AdjLayout adj_layout(const lbm_ctx* ctx, int k, int segs, bool recompute) {
     L.pop = round_up(pop_bytes(ctx));
     L.mom_step = round_up(static_cast<size_t>(ctx->N) * (ctx->D + 2) * elem_bytes(ctx->prec));
     L.off_mom = 3 * L.pop;
-    L.nA = lbm::step_blocks(ctx->model, ctx->prec, adjoint_params(ctx));
+    L.nA = lbm::step_blocks(ctx->model, ctx->prec, adjoint_params(ctx, kAdjoint));
     L.nK = (ctx->N + 255) / 256;
     L.off_partA = L.off_mom + (recompute ? static_cast<size_t>(k) * L.mom_step : 0);
     L.off_partK = L.off_partA + round_up(static_cast<size_t>(L.nA) * 8);
@@ -1192,7 +1240,8 @@ LBM_API int lbm_adjoint(lbm_ctx* ctx, int n, int k, int keep, const void* ckpt,
         return fail(ctx, LBM_E_INVALID, "workspace must be 256-byte aligned");
     if ((rc = set_device(ctx)) != LBM_OK) return rc;
 
-    const lbm::KParams kab = adjoint_params(ctx);
+    const lbm::KParams kab = adjoint_params(ctx, kAdjoint);
+    const lbm::KParams kstep = adjoint_params(ctx, kSteps);   // recomputed steps
     char* ws = static_cast<char*>(workspace);
     void* B[3] = {ws, ws + L.pop, ws + 2 * L.pop};
     char* mom = ws + L.off_mom;
@@ -1239,7 +1288,7 @@ LBM_API int lbm_adjoint(lbm_ctx* ctx, int n, int k, int keep, const void* ckpt,
             const void* src = ck + s * ck_stride;
             int dst = fr[0];
             for (int j = 0; j < len; ++j) {
-                e = lbm::launch_step(ctx->model, ctx->prec, kab, src,
+                e = lbm::launch_step(ctx->model, ctx->prec, kstep, src,
                                      j + 1 < len ? B[dst] : nullptr, mom + j * L.mom_step, st);
                 if (e != hipSuccess) return fail_hip(ctx, e, "recompute step kernel");
                 src = B[dst];

@@ -142,6 +142,7 @@ struct KParams {
     int chunks;               // blocks per grid row (x direction); flat: per row group
     int rpb;                  // grid rows per block (> 1 only with chunks = 1, nx % 64 = 0)
     int bx;                   // threads per block (multiple of 64)
+    int resident;             // blocks a CU holds at once, 1 or 2 (0: as many as fit)
     FastDiv by_nx, by_ny, by_gpp, by_chunks;
     unsigned inv_nx, inv_ny, inv_nz;   // 65536 / n + 1 (axes of at most kMaxDisp cells)
     int xcd_cyclic;           // > 0: the forward steps hand the 8 XCDs chunks of this

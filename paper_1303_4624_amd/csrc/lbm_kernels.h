@@ -1475,6 +1475,21 @@ hipError_t with_initial_form(const KParams& kp, F&& f) {
     return f(std::integral_constant<int, kFormAB>{});
 }
 
+// Dynamic LDS that lets a CU (160 KB) hold `resident` blocks at once; 0: no
+// limit.  More than 64 KB has to be allowed for the kernel first.
+template <class K>
+unsigned limit_blocks(K kernel, int resident) {
+    if (resident <= 0) return 0;
+    if (resident > 1) return 64u * 1024u * 2u / static_cast<unsigned>(resident);
+    constexpr int bytes = 96 * 1024;
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        return 64u * 1024u;
+    }
+    return bytes;
+}
+
 // Calls f with std::bool_constant<kp.flat>, std::bool_constant<kp.nt>.
 template <class F>
 void with_route(const KParams& kp, F&& f) {
@@ -1546,7 +1561,7 @@ hipError_t ModelKernels<M, PR>::step(const KParams& kp, const void* src, void* d
     }
     const dim3 grid(static_cast<unsigned>(step_blocks(M::id, PR, kp)));
     const auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, grid, dim3(kp.bx), 0, s,
+        hipLaunchKernelGGL(kernel, grid, dim3(kp.bx), limit_blocks(kernel, kp.resident), s,
                            static_cast<const S*>(src), static_cast<S*>(dst), kp,
                            static_cast<S*>(mom_out));
     };
@@ -1573,7 +1588,8 @@ hipError_t ModelKernels<M, PR>::step_aa(const KParams& kp, void* f, bool push, v
     using S = typename P::S;
     const dim3 grid(static_cast<unsigned>(step_blocks(M::id, PR, kp)));
     const auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, grid, dim3(kp.bx), 0, s, static_cast<S*>(f), kp,
+        hipLaunchKernelGGL(kernel, grid, dim3(kp.bx), limit_blocks(kernel, kp.resident), s,
+                           static_cast<S*>(f), kp,
                            static_cast<S*>(mom_out));
     };
     const bool hold = kp.hold_lo + kp.hold_hi > 0;
@@ -1661,7 +1677,8 @@ hipError_t ModelKernels<M, PR>::adjoint_step(const KParams& kp, const void* lam_
     using S = typename P::S;
     const long long blocks = step_blocks(M::id, PR, kp);
     const auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(kp.bx), 0, s,
+        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(kp.bx),
+                           limit_blocks(kernel, kp.resident), s,
                            static_cast<const S*>(lam_src), static_cast<S*>(lam_dst),
                            static_cast<const S*>(mom), kp, partA,
                            static_cast<const S*>(mark_state), partM);

@@ -240,7 +240,8 @@ void fill_layout(const lbm_ctx* ctx, KParams& k) {
     // 64^3 (199 MB) 38.9, 30.7; 64x64x96 (299 MB) 63.7, 60.2; 64x64x128 (398 MB)
     // 80.6, 78.4; 64x64x160 (498 MB) 100.6, 101.7; 128x128x64 (797 MB) 157.9,
     // 162.7; float64 64x64x32 (199 MB) 38.4, 31.9; in place 64x64x128 (199 MB)
-    // 64.9, 58.7 and 128x128x64 (398 MB) 129.9, 134.2; D2Q33 512^2 15.0, 12.5.
+    // 64.9, 58.7, 64x64x160 (249 MB) 75.8, 74.4, float64 128^3 D3Q19 (319 MB) 93.6,
+    // 95.6 and 128x128x64 (398 MB) 129.9, 134.2; D2Q33 512^2 15.0, 12.5.
     const long long state = static_cast<long long>(k.gs) * k.gpp * k.nz * bytes;
     // Between those, D3Q95 with two buffers of 16 to 40 MB: the L2s (8 of 4 MB)
     // hold a whole step's output and write it back at the kernel's end, which
@@ -249,7 +250,7 @@ void fill_layout(const lbm_ctx* ctx, KParams& k) {
     // 40^3, 49 MB: 17.9, 13.5).  The smaller sets gain nothing (D3Q15 64^3, 31
     // MB: 7.2 against 6.6 us).
     const long long moved = ctx->aa ? state : 2 * state;
-    k.nt = moved > lbm::kCachedState ||
+    k.nt = moved > (ctx->aa ? lbm::kCachedStateInPlace : lbm::kCachedState) ||
            (!ctx->aa && ctx->Q >= 95 && moved > lbm::kL2StateLo && moved <= lbm::kL2StateHi);
 }
 
@@ -294,8 +295,9 @@ enum BlockUse { kSteps, kStepsInPlace, kAdjoint };
 // In place the writes hit lines other blocks read: D3Q95 FP32-shifted two
 // blocks of 128 from 1 GB (256^3 2411, 2323; 384^3 8260, 8010; 170x145x141 525,
 // 506), below that blocks of 256 alone (128^3 298, 286, held 289; 128x128x90
-// 192, 191, held 203); float64 one of 256 on flat groups (200^3 2439, 2322),
-// none by rows (256^3 4786, held 4829); the smaller sets two of 256 (D2Q33
+// 192, 191, held 203); float64 one of 192 or of a flat group (200^3 2439, 2322;
+// 192^3 2126, 2028; 320x320x200 6289, 5801), of 256 not (256^3 4786, held 4829);
+// the smaller sets two of 256 (D2Q33
 // 2000^2 204, 191, float64 398, 377; D3Q19 256^3 471, 446).  The cache prefers
 // many waves (64^3 FP32-shifted 30, held 49), and so does the adjoint's mix of
 // arithmetic and loads (128^3, 40 steps: 18.5 ms with and without).
@@ -318,7 +320,7 @@ void set_blocks(const lbm_ctx* ctx, KParams& k, BlockUse use) {
             most = flat_most = k.resident ? 128 : 256;
         } else if (ctx->Q >= 95) {
             flat_most = most;
-            k.resident = k.flat ? 1 : 0;
+            k.resident = 1;
         } else if (ctx->Q >= 33 && use == kSteps && !f64) {
             flat_most = most;
             k.resident = 1;
@@ -334,7 +336,29 @@ void set_blocks(const lbm_ctx* ctx, KParams& k, BlockUse use) {
         k.chunks = (group + flat_most / 64 - 1) / (flat_most / 64);
         k.bx = (group + k.chunks - 1) / k.chunks * 64;
     } else {
-        const lbm::RowLaunch rl = lbm::row_launch(k.nx, rows, most);
+        // a held row that its blocks would leave a tenth short of lanes takes
+        // larger ones (D3Q95 in place 192^3: 1115 us with 2 blocks of 128 a row,
+        // 1025 with one of 192)
+        const auto short_of = [&](int m) {
+            const lbm::RowLaunch r = lbm::row_launch(k.nx, rows, m);
+            return 10LL * r.chunks * r.bx > 11LL * k.nx;
+        };
+        int fit = most;
+        if (k.resident && short_of(most)) {
+            const int limit = lbm::step_max_threads(ctx->model, ctx->prec);
+            while (fit < limit && short_of(fit)) fit += 64;
+            if (short_of(fit)) fit = most;
+        }
+        const lbm::RowLaunch rl = lbm::row_launch(k.nx, rows, fit);
+        // 4 waves of D3Q95 a CU in place, 8 to 12 of the smaller sets (D3Q19
+        // 320x200x200 with 5 waves 427 us, 342 unlimited; D3Q15 384x200x200 with 6
+        // 354, 327)
+        if (k.resident && ctx->Q >= 95 && use == kStepsInPlace) {
+            if (f64) k.resident = rl.bx < 256 ? 1 : 0;
+            else if (rl.bx > 256) k.resident = 1;
+        } else if (k.resident && ctx->Q < 95) {
+            k.resident = (8 + rl.bx / 64 - 1) / (rl.bx / 64);
+        }
         k.chunks = rl.chunks;
         k.bx = rl.bx;
         if (lbm::kPackRows && k.nx % 64 == 0) {
@@ -619,10 +643,22 @@ void drop_graph(lbm_ctx* ctx) {
     ctx->graph_cur = ctx->graph_form = -1;
 }
 
+// Every second in-place step takes the cells backwards: the cache still holds
+// what the step before it touched last, which a sweep in the same direction
+// reaches only after evicting it (us per step, same direction against
+// alternating: D2Q33 FP32-shifted 2048^2 (554 MB) 198, 167; 4096^2 772, 739; D3Q19
+// 200^3 220, 195; D3Q95 128^3 284, 274).  States past 4 GB gain nothing (256^3
+// FP32-shifted, 6.4 GB: 2322, 2337), nor do two buffers, where a step reads what
+// the cache has not kept: it fills on reads (128^3 282, 282).
+int reverse_step(const lbm_ctx* ctx) {
+    return ctx->kp.form == lbm::kFormPushed && pop_bytes(ctx) <= (size_t{4} << 30);
+}
+
 // One update step on the context's stream (two-buffer or in place).
 hipError_t launch_one_step(lbm_ctx* ctx) {
     if (ctx->aa) {
         const bool push = ctx->kp.form == lbm::kFormSwapped;
+        ctx->kp.reverse = reverse_step(ctx);
         hipError_t e =
             lbm::launch_step_aa(ctx->model, ctx->prec, ctx->kp, ctx->f[0], push, nullptr,
                                 ctx->stream);
@@ -1092,6 +1128,7 @@ LBM_API int lbm_run_checkpointed(lbm_ctx* ctx, int n, int k, int keep, void* ckp
         for (int t = 0; t < n; ++t) {
             void* mom = (t >= c.t_keep) ? ck + c.off_tail + (t - c.t_keep) * c.mom_step : nullptr;
             const bool push = ctx->kp.form == lbm::kFormSwapped;
+            ctx->kp.reverse = reverse_step(ctx);
             e = lbm::launch_step_aa(ctx->model, ctx->prec, ctx->kp, ctx->f[0], push, mom,
                                     ctx->stream);
             if (e != hipSuccess) return fail_hip(ctx, e, "in-place step kernel");
@@ -1162,6 +1199,7 @@ namespace {
 KParams adjoint_params(const lbm_ctx* ctx, BlockUse use) {
     KParams k = ctx->kp;
     k.form = lbm::kFormAB;
+    k.reverse = 0;
     set_blocks(ctx, k, use);
     k.xcd_cyclic = ctx->mapping ? cyclic_chunk(k, ctx->D) : 0;
     return k;

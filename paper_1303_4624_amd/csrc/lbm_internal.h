@@ -58,6 +58,7 @@ constexpr int kFlatCells = 384;
 // Bytes of populations up to which a step's stores stay in the cache (256 MB
 // shared by all XCDs); see fill_layout.
 constexpr long long kCachedState = 384LL << 20;
+constexpr long long kCachedStateInPlace = 256LL << 20;   // one buffer
 constexpr long long kL2StateLo = 16LL << 20;
 constexpr long long kL2StateHi = 40LL << 20;
 
@@ -142,9 +143,10 @@ struct KParams {
     int chunks;               // blocks per grid row (x direction); flat: per row group
     int rpb;                  // grid rows per block (> 1 only with chunks = 1, nx % 64 = 0)
     int bx;                   // threads per block (multiple of 64)
-    int resident;             // blocks a CU holds at once, 1 or 2 (0: as many as fit)
+    int resident;             // blocks a CU holds at once (0: as many as fit)
     FastDiv by_nx, by_ny, by_gpp, by_chunks;
     unsigned inv_nx, inv_ny, inv_nz;   // 65536 / n + 1 (axes of at most kMaxDisp cells)
+    int reverse;              // 1: this launch takes the blocks from the last to the first
     int xcd_cyclic;           // > 0: the forward steps hand the 8 XCDs chunks of this
                               // many blocks in turn; 0: a contiguous range each
     long long N;              // cells

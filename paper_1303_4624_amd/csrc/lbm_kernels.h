@@ -283,22 +283,25 @@ struct PopAt<M, kFormPushed> {
 // 8 * xcd_cyclic blocks, the XCDs take chunks of xcd_cyclic blocks in turn
 // instead.  Which of the two is faster depends on where the buffers lie in
 // HBM (lbm_tune_step measures it).
+// k.reverse: each XCD takes its blocks from the last to the first.
 template <bool FLAT, class S, bool CYCLIC = false>
 __device__ __forceinline__ Cell row_cell(const KParams& k) {
 #if LBM_XCD_REMAP
     const int hb = blockIdx.x;
     const int nb = gridDim.x;
-    const int xcd = hb & 7, pos = hb >> 3;
+    const int xcd = hb & 7, q = nb >> 3, r = nb & 7;
+    int pos = hb >> 3;
+    if (k.reverse) pos = q - (xcd < r ? 0 : 1) - pos;
     const int cc = CYCLIC ? k.xcd_cyclic : 0;
     int b;
     if (cc > 0 && nb % (8 * cc) == 0) {
         b = ((pos / cc) * 8 + xcd) * cc + pos % cc;
     } else {
-        const int q = nb >> 3, r = nb & 7;
         b = (xcd < r) ? xcd * (q + 1) + pos : r * (q + 1) + (xcd - r) * q + pos;
     }
 #else
-    const int b = blockIdx.x;
+    const int nb = gridDim.x;
+    const int b = k.reverse ? nb - 1 - static_cast<int>(blockIdx.x) : blockIdx.x;
 #endif
     Cell cl;
     if constexpr (FLAT) {

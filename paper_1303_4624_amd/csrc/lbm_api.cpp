@@ -370,6 +370,12 @@ void set_blocks(const lbm_ctx* ctx, KParams& k, BlockUse use) {
         }
     }
     set_divisors(k);
+    // D3Q95 steps of so few waves that even four times as many leave the CUs two
+    // each: four share the work of one (k_step_split; us per step float64 64x8x8
+    // 7.3, 5.9; 512x4x4 (128 waves) 8.5, 7.7; 210x5x9 (153) 9.0, 9.8;
+    // FP32-shifted 12^3 7.5, 5.6; 512x4x4 7.3, 6.2; 20^3 (140) 7.4, 8.1).
+    k.split = few && ctx->Q >= 95 && use == kSteps &&
+              lbm::step_blocks(ctx->model, ctx->prec, k) * 2 <= lbm::kCUs;
 }
 
 // Strips of a narrow 2D grid (k_steps_strip): steps per launch and strip width

@@ -62,6 +62,9 @@ constexpr long long kCachedStateInPlace = 256LL << 20;   // one buffer
 constexpr long long kL2StateLo = 16LL << 20;
 constexpr long long kL2StateHi = 40LL << 20;
 
+// Blocks of one wave that share 64 cells in k_step_split.
+constexpr int kSplit = 4;
+
 // Grids of at most this many waves take blocks of one wave.
 constexpr int kFewWaves = 4096;
 
@@ -143,6 +146,7 @@ struct KParams {
     int chunks;               // blocks per grid row (x direction); flat: per row group
     int rpb;                  // grid rows per block (> 1 only with chunks = 1, nx % 64 = 0)
     int bx;                   // threads per block (multiple of 64)
+    int split;                // 1: kSplit blocks share the cells of one (two buffers)
     int resident;             // blocks a CU holds at once (0: as many as fit)
     FastDiv by_nx, by_ny, by_gpp, by_chunks;
     unsigned inv_nx, inv_ny, inv_nz;   // 65536 / n + 1 (axes of at most kMaxDisp cells)

@@ -285,10 +285,9 @@ struct PopAt<M, kFormPushed> {
 // HBM (lbm_tune_step measures it).
 // k.reverse: each XCD takes its blocks from the last to the first.
 template <bool FLAT, class S, bool CYCLIC = false>
-__device__ __forceinline__ Cell row_cell(const KParams& k) {
+__device__ __forceinline__ Cell row_cell(const KParams& k, int hb, int nb) {
+    const int tid = static_cast<int>(threadIdx.x);
 #if LBM_XCD_REMAP
-    const int hb = blockIdx.x;
-    const int nb = gridDim.x;
     const int xcd = hb & 7, q = nb >> 3, r = nb & 7;
     int pos = hb >> 3;
     if (k.reverse) pos = q - (xcd < r ? 0 : 1) - pos;
@@ -300,15 +299,14 @@ __device__ __forceinline__ Cell row_cell(const KParams& k) {
         b = (xcd < r) ? xcd * (q + 1) + pos : r * (q + 1) + (xcd - r) * q + pos;
     }
 #else
-    const int nb = gridDim.x;
-    const int b = k.reverse ? nb - 1 - static_cast<int>(blockIdx.x) : blockIdx.x;
+    const int b = k.reverse ? nb - 1 - hb : hb;
 #endif
     Cell cl;
     if constexpr (FLAT) {
         const int gi = div_by(b, k.by_chunks);
         const int z = div_by(gi, k.by_gpp), y0 = (gi - z * k.gpp) << k.rg_shift;
         const int cells = (k.ny - y0 < k.rg ? k.ny - y0 : k.rg) * k.nx;
-        const int j = (b - gi * k.chunks) * k.bx + static_cast<int>(threadIdx.x);
+        const int j = (b - gi * k.chunks) * k.bx + tid;
         constexpr int line = kLineBytes / static_cast<int>(sizeof(S));
         const int whole = (cells + line - 1) / line * line;
         const int lim = whole < k.ps ? whole : k.ps;
@@ -326,12 +324,12 @@ __device__ __forceinline__ Cell row_cell(const KParams& k) {
         if (kPackRows && k.rpb > 1) {
             // rpb whole rows of nx (a multiple of 64) lanes: the row is uniform
             // over each wave
-            const int sub = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / k.nx);
+            const int sub = __builtin_amdgcn_readfirstlane(tid / k.nx);
             row = b * k.rpb + sub;
-            x = static_cast<int>(threadIdx.x) - sub * k.nx;
+            x = tid - sub * k.nx;
         } else {
             row = div_by(b, k.by_chunks);
-            x = (b - row * k.chunks) * k.bx + static_cast<int>(threadIdx.x);
+            x = (b - row * k.chunks) * k.bx + tid;
         }
         cl.active = x < k.nx;
         cl.idle = x >= k.lim;
@@ -496,6 +494,9 @@ struct PlaneWriter {
     __device__ __forceinline__ void put(S val) {
         store_pop<S, NT>(run + off, val);
         run += runb;
+    }
+    __device__ __forceinline__ void put_at(int i, S val) const {
+        store_pop<S, NT>(run + i * runb + off, val);
     }
 };
 
@@ -729,6 +730,33 @@ template <class M, class P, class Emit>
 __device__ __forceinline__ void relax_with(const KParams& k, const typename P::S (&v)[M::Q],
                                            const Macro& mc, Emit&& emit);
 
+// Groups dealt to SPLIT parts of about equal numbers of velocities: largest
+// first, each to the part that has fewest.
+template <class M, int SPLIT>
+struct SplitGroups {
+    struct Arr {
+        int v[M::G];
+    };
+    static constexpr Arr make() {
+        Arr a{};
+        int load[SPLIT] = {};
+        bool done[M::G] = {};
+        for (int n = 0; n < M::G; ++n) {
+            int g = -1;
+            for (int c = 0; c < M::G; ++c)
+                if (!done[c] && (g < 0 || M::table.gsize[c] > M::table.gsize[g])) g = c;
+            int p = 0;
+            for (int c = 1; c < SPLIT; ++c)
+                if (load[c] < load[p]) p = c;
+            done[g] = true;
+            a.v[g] = p;
+            load[p] += M::table.gsize[g];
+        }
+        return a;
+    }
+    static constexpr Arr part = make();
+};
+
 template <class M, class P, class Emit>
 __device__ __forceinline__ Macro relax_cell(const KParams& k, const typename P::S (&v)[M::Q],
                                             Emit&& emit) {
@@ -737,8 +765,9 @@ __device__ __forceinline__ Macro relax_cell(const KParams& k, const typename P::
     return mc;
 }
 
-template <class M, class P, class Emit>
-__device__ __forceinline__ void relax_with(const KParams& k, const typename P::S (&v)[M::Q],
+// PART of SPLIT: only the groups that fall to it (see SplitGroups).
+template <class M, class P, int SPLIT, int PART, class Emit>
+__device__ __forceinline__ void relax_part(const KParams& k, const typename P::S (&v)[M::Q],
                                            const Macro& mc, Emit&& emit) {
     using R = typename P::S;
     constexpr int G = M::G;
@@ -751,6 +780,7 @@ __device__ __forceinline__ void relax_with(const KParams& k, const typename P::S
 
     static_for<G>([&](auto GI) {
         constexpr int g = decltype(GI)::value;
+        if constexpr (SPLIT > 1 && SplitGroups<M, SPLIT>::part.v[g] != PART) return;
         const GCoef gc = xp.at(group_x<M, g>(k));
         const R a0 = R(gc.a0), a1 = R(gc.a1), a2 = R(gc.a2);
         const R ca = R(wr * k.W[g]);
@@ -769,6 +799,12 @@ __device__ __forceinline__ void relax_with(const KParams& k, const typename P::S
             emit(std::integral_constant<int, i>{}, out);
         });
     });
+}
+
+template <class M, class P, class Emit>
+__device__ __forceinline__ void relax_with(const KParams& k, const typename P::S (&v)[M::Q],
+                                           const Macro& mc, Emit&& emit) {
+    relax_part<M, P, 1, 0>(k, v, mc, emit);
 }
 
 // Forward update, two buffers: pull gather from src, relax, store to dst.
@@ -807,7 +843,7 @@ void k_step(const typename P::S* __restrict__ src, typename P::S* __restrict__ d
     using S = typename P::S;
     constexpr int D = M::D;
     static_assert(POP || STORE_MOM, "a step stores populations, moments or both");
-    const Cell cl = row_cell<FLAT, S, true>(k);
+    const Cell cl = row_cell<FLAT, S, true>(k, blockIdx.x, gridDim.x);
     if (cl.idle) return;
 
     if constexpr (HOLD) {
@@ -846,6 +882,42 @@ void k_step(const typename P::S* __restrict__ src, typename P::S* __restrict__ d
     }
 }
 
+// k_step for grids that leave most CUs idle: kSplit blocks of one wave share 64
+// cells.  Each gathers all velocities and forms the moments (the same sums in
+// the same order, so the result is the same bits), then relaxes and stores its
+// share of the groups: a step takes as long as one wave's instructions, of
+// which relaxation and stores are half.  As waves of one block, on one CU, the
+// four gathers take the time that is saved (float64 512x4x4 8.9 us per step,
+// 7.7 as blocks, 8.5 unsplit).
+template <class M, class P, bool FLAT, bool HOLD>
+__global__ __launch_bounds__(64) void k_step_split(
+    const typename P::S* __restrict__ src, typename P::S* __restrict__ dst, KParams k) {
+    using S = typename P::S;
+    const int nb = static_cast<int>(gridDim.x) / kSplit;
+    const int part = static_cast<int>(blockIdx.x) / nb;
+    const Cell cl = row_cell<FLAT, S, true>(k, static_cast<int>(blockIdx.x) - part * nb, nb);
+    if (cl.idle) return;
+    const PlaneWriter<S, FLAT, false> out(dst, k, cl);
+    const auto put = [&](auto I, S val) { out.put_at(decltype(I)::value, val); };
+    if constexpr (HOLD) {
+        const int sl = (M::D == 3) ? cl.z : cl.y;
+        const int L = (M::D == 3) ? k.nz : k.ny;
+        if (sl < k.hold_lo || sl >= L - k.hold_hi) {
+            const FixedState& st = (sl < k.hold_lo) ? k.hold[0] : k.hold[1];
+            if (part == 0)
+                feq_cell<M, P>(k, st.rho, st.U[0], st.U[1], st.U[2], st.T, put);
+            return;
+        }
+    }
+    S v[M::Q];
+    gather<M, +1, FLAT>(src, k, cl, v);
+    const Macro mc = cell_macro_pinned<M, P>(k, v);
+    static_for<kSplit>([&](auto PI) {
+        constexpr int p = decltype(PI)::value;
+        if (part == p) relax_part<M, P, kSplit, p>(k, v, mc, put);
+    });
+}
+
 // Forward update in place on one buffer (AA pattern).  The buffer holds the
 // post-collision state f* of the current step in one of two forms:
 //   swapped : f*_i(x) in run opp(i) of cell x,
@@ -868,7 +940,7 @@ __global__ __launch_bounds__(row_block_limit(M::Q, P::id)) __attribute__((amdgpu
 void k_step_aa(typename P::S* f, KParams k, typename P::S* __restrict__ mom) {
     using S = typename P::S;
     constexpr int D = M::D;
-    const Cell cl = row_cell<FLAT, S, true>(k);
+    const Cell cl = row_cell<FLAT, S, true>(k, blockIdx.x, gridDim.x);
     SlabAddr<M, S, char, FLAT, true> ad(reinterpret_cast<char*>(f), k, cl);
     const auto put = [&](auto I, S val) {
         constexpr int i = decltype(I)::value;
@@ -1273,7 +1345,7 @@ void k_adjoint(const typename P::S* __restrict__ lsrc, typename P::S* __restrict
     constexpr int Q = M::Q;
     constexpr int G = M::G;
     constexpr int D = M::D;
-    Cell cl = row_cell<FLAT, S>(k);
+    Cell cl = row_cell<FLAT, S>(k, blockIdx.x, gridDim.x);
     // by rows, surplus lanes repeat the store of the row's last cell: one
     // register less than filling its line, which keeps 3 waves per SIMD
     if constexpr (!FLAT) cl.at = cl.x;
@@ -1563,6 +1635,22 @@ hipError_t ModelKernels<M, PR>::step(const KParams& kp, const void* src, void* d
         }
     }
     const dim3 grid(static_cast<unsigned>(step_blocks(M::id, PR, kp)));
+    if constexpr (M::Q >= 95) {
+        if (kp.split && !mom_out) {
+            const auto go = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, dim3(grid.x * kSplit), dim3(64), 0, s,
+                                   static_cast<const S*>(src), static_cast<S*>(dst), kp);
+            };
+            if (kp.flat) {
+                if (hold) go(k_step_split<M, P, true, true>);
+                else go(k_step_split<M, P, true, false>);
+            } else {
+                if (hold) go(k_step_split<M, P, false, true>);
+                else go(k_step_split<M, P, false, false>);
+            }
+            return hipGetLastError();
+        }
+    }
     const auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, dim3(kp.bx), limit_blocks(kernel, kp.resident), s,
                            static_cast<const S*>(src), static_cast<S*>(dst), kp,

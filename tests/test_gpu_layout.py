@@ -24,6 +24,8 @@ EXTENTS = [
     ("D3Q95", (383, 5, 2)),       # the longest flat rows
     ("D3Q95", (385, 5, 2)),       # stored by rows, surplus lanes on the padding
     ("D3Q95", (128, 12, 3)),      # rows packed into blocks, groups of four rows
+    ("D3Q95", (512, 4, 4)),       # 128 waves: the most whose work is split
+    ("D3Q95", (192, 43, 1)),      # 129
     ("D2Q33", (11, 200)),         # 2D: groups of 128 rows
     ("D2Q33", (5, 3)),
     ("D2Q33", (383, 9)),

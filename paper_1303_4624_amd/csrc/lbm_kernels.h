@@ -55,10 +55,6 @@ namespace {
 
 // Build-time switches, each at its measured best (alternatives timed on the
 // same buffers unless noted):
-// non-temporal stores of the two-buffer steps (plain stores 4-8 % slower);
-#ifndef LBM_NT_STORE
-#define LBM_NT_STORE 1
-#endif
 // non-temporal loads (8 % slower);
 #ifndef LBM_NT_LOAD
 #define LBM_NT_LOAD 0
@@ -75,19 +71,16 @@ namespace {
 #define LBM_ADJ_WAVES 3
 #endif
 // minimum waves per SIMD of the FP32-shifted steps (the compiler's budget;
-// they hold 125-172 VGPRs);
+// they hold 126-170 VGPRs);
 #ifndef LBM_F32_WAVES
 #define LBM_F32_WAVES 1
 #endif
 // the pushed stores of the AA kernel start at x + e_x, off the 128-byte line
 // grid; plain stores let L2 merge the partial lines of neighbouring waves
-// before they reach HBM (non-temporal 8 % slower); its own-row stores are
-// non-temporal like the two-buffer step's;
+// before they reach HBM (non-temporal 8 % slower; its own-row stores go by the
+// state's size like the two-buffer step's, KParams::nt);
 #ifndef LBM_AA_NT_PUSH
 #define LBM_AA_NT_PUSH 0
-#endif
-#ifndef LBM_AA_NT_LOCAL
-#define LBM_AA_NT_LOCAL 1
 #endif
 // float64 moment sums of the FP32-shifted storage (see F32ST).
 #ifndef LBM_F32S_SUM64
@@ -406,7 +399,7 @@ __device__ __forceinline__ S load_pop(const char* p) {
 #endif
 }
 
-template <class S, bool NT = (LBM_NT_STORE != 0)>
+template <class S, bool NT>
 __device__ __forceinline__ void store_pop(char* p, S val) {
     if constexpr (NT)
         __builtin_nontemporal_store(val, reinterpret_cast<S*>(p));

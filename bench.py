@@ -554,6 +554,8 @@ def _instance(name: str):
     model = args[0] if args and args[0] in _MODEL_QD else None
     prec = {"F32ST": "F32S", "F64T": "F64"}.get(args[1]) if len(args) > 1 else None
     flags = tuple(int(a == "true") for a in args[2:] if a in ("true", "false"))
+    if m.group(1) in _ROW_KERNELS and len(flags) == 5:
+        flags = flags[2:]                       # FLAT, NT: the same work and bytes
     return m.group(1), model, prec, flags
 
 

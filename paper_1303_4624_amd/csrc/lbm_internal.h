@@ -62,6 +62,18 @@ constexpr long long kCachedStateInPlace = 256LL << 20;   // one buffer
 constexpr long long kL2StateLo = 16LL << 20;
 constexpr long long kL2StateHi = 40LL << 20;
 
+// LDS a block reserves so that a CU holds `blocks` of them at once, no more and
+// no fewer: the smallest number of allocation units that blocks + 1 of do not
+// fit.  0: no limit.  Past kMaxHeld the units are too coarse to tell.
+constexpr int kLdsBytes = 160 * 1024;   // of a CU
+constexpr int kLdsUnit = 1280;
+constexpr int kMaxHeld = 12;
+constexpr int held_lds_bytes(int blocks) {
+    return blocks > 0 && blocks <= kMaxHeld
+               ? (kLdsBytes / kLdsUnit / (blocks + 1) + 1) * kLdsUnit
+               : 0;
+}
+
 // Blocks of one wave that share 64 cells in k_step_split.
 constexpr int kSplit = 4;
 

@@ -1543,19 +1543,19 @@ hipError_t with_initial_form(const KParams& kp, F&& f) {
     return f(std::integral_constant<int, kFormAB>{});
 }
 
-// Dynamic LDS that lets a CU (160 KB) hold `resident` blocks at once; 0: no
-// limit.  More than 64 KB has to be allowed for the kernel first.
+// Dynamic LDS that lets a CU hold `resident` blocks at once; 0: no limit.  More
+// than 64 KB (one block) has to be allowed for the kernel first.
 template <class K>
 unsigned limit_blocks(K kernel, int resident) {
-    if (resident <= 0) return 0;
-    if (resident > 1) return 64u * 1024u * 2u / static_cast<unsigned>(resident);
-    constexpr int bytes = 96 * 1024;
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+    constexpr int granted = 64 * 1024;
+    const int bytes = held_lds_bytes(resident);
+    if (bytes > granted &&
+        hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                             hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) {
         (void)hipGetLastError();
-        return 64u * 1024u;
+        return granted;
     }
-    return bytes;
+    return static_cast<unsigned>(bytes);
 }
 
 // Calls f with std::bool_constant<kp.flat>, std::bool_constant<kp.nt>.

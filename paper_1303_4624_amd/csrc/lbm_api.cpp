@@ -276,6 +276,56 @@ void set_divisors(KParams& k) {
 // Kernels that share a block size.
 enum BlockUse { kSteps, kStepsInPlace, kAdjoint };
 
+// Cells that the blocks a CU holds at once have together at least, where they are
+// held (see set_blocks).  Cells and not blocks are counted, since a short row or
+// a thin plane may give a block only a few.  us per step by blocks per CU (- not
+// measured; * what the rule takes):
+//                       cells    1    2    3    4    6    8  unlimited
+//   D3Q95 FP32-shifted
+//     64x251x251           64  1308  720  573  541  549  553  564   *5
+//     11x11x5000          121   138  100  *94   94   95   94   94
+//     128x129x129         128   397  301 *293  296  302  301  300
+//     192x129x129         192   487 *442  444  448  454  454  455
+//     256x129x129         256   600 *583  594  601  601  601  601
+//     320x111x111         320  *540  546  549  549  549  549  549
+//   D3Q95 float64
+//     5x5x20000            25   491  262  209  182 *167  168  168
+//     64x251x251           64  1522 1110*1094 1102 1120 1119 1120
+//     11x11x10000         121   376 *342  352  353  353    -  353
+//     11x11x20000         121   782 *814  870  782  764    -  763
+//     128x129x129         128   639 *585  597  599  597  598  598
+//     320x128x128         160 *1452 1484 1509 1509 1510    - 1510
+//     192x129x129         192  *868  891  896  896  896  896  897
+//   D3Q95 FP32-shifted in place
+//     64x251x251           64  1203  666  561 *552  553  557  549
+//     16x11x20000          88   827  561 *519  522  566    -  569
+//     400x128x128         100  1362 1017 *993 1021 1078    - 1058
+//     777x101x101         111  1487 1166*1179 1213 1274    - 1232
+//     100x200x200         115   727 *576  580  599  625    -  598
+//     128x200x200         128     - *704  711  724  729  732  731
+//     192x200x200         192     -*1095 1115 1123 1121 1119 1120
+//   smaller sets, FP32-shifted
+//     D3Q19 64x511x511     64     - 1154  815  634  465 *417  447
+//     D3Q19 192x256x256   192     -  381 *322  327  332  334  342
+//     D3Q19 400x160x160   200   430  292 *275  283  289    -  291
+//     D3Q19 128x256x256   256     - *214  217  218  221  225  225
+//     D2Q33 384x30000     384   557 *518  527  526  528    -  527
+//     D2Q33 256x50000     512  *556  582  580  593  593    -  592
+//     D3Q15 200^3         229   277  174 *163  164  168    -  172
+//     D3Q15 256x200x200   256   318  212 *207  211  210    -  215
+//     D3Q15 384x160x160   192   395  232  204 *202  208    -  210
+//   smaller sets, float64 (two blocks at least)
+//     D3Q19 5x5x200000     25     -  751  540  449  377  334  331  *10
+//     D3Q19 11x11x60000   121   522 *392  414  430  462    -  439
+//     D3Q19 400x160x160   200   673 *536  560  567  581    -  581
+//     D3Q15 384x160x160   192   497 *406  417  422  421    -  425
+//     D3Q15 256x200x200   256   506 *415  417  420  422    -  423
+int held_cells(const lbm_ctx* ctx, BlockUse use) {
+    const bool f64 = ctx->prec == Prec::F64;
+    if (ctx->Q >= 95) return f64 ? 150 : use == kStepsInPlace ? 230 : 300;
+    return f64 ? 240 : ctx->Q >= 19 ? 450 : 600;
+}
+
 // Blocks of the kernels that advance cells: their size, and how many a CU holds
 // at once (k.resident).
 //
@@ -285,22 +335,24 @@ enum BlockUse { kSteps, kStepsInPlace, kAdjoint };
 // 5.3; 400^2 16.0, 15.1; from 64^3 on the same).
 //
 // States past the cache (k.nt) are bound by HBM, whose rate falls as more waves
-// read and write their own places in it at once: a CU is held to 4 to 8 waves,
-// in the fewest blocks.  us per step, unlimited against held, on the same
-// buffers: D3Q95 FP32-shifted one block of 512 or a 384-cell row (128^3 292,
-// 281; 256^3 2258, 2182; 384^3 7770, 7503; 200^3 1144, 1105), float64 one of 256
-// (256^3 4440, 4285; 150^3 937, 898); D2Q33 FP32-shifted one of 512 (2393x3579
-// 403, 388; 8192^2 2914, 2867), float64 two of 256 (814, 788); D3Q19
-// FP32-shifted two of 256 (256^3 438, 416), float64 the same (889, 856).
+// read and write their own places in it at once, and which too few do not fill:
+// a CU is held to the fewest blocks that have held_cells() cells.  us per step,
+// unlimited against held, on the same buffers: D3Q95 FP32-shifted one block
+// of 512 or a 384-cell row (128^3 292, 281; 256^3 2260, 2188; 384^3 7770, 7505;
+// 200^3 1144, 1105), float64 one of 256 (256^3 4468, 4315; 150^3 937, 898); D2Q33
+// FP32-shifted one of 512 (2393x3579 403, 388; 8192^2 2914, 2867), float64 two of
+// 256 (814, 788); D3Q19 FP32-shifted two of 256 (256^3 438, 416), float64 the same
+// (889, 856).
 // In place the writes hit lines other blocks read: D3Q95 FP32-shifted two
-// blocks of 128 from 1 GB (256^3 2411, 2323; 384^3 8260, 8010; 170x145x141 525,
+// blocks of 128 from 1 GB (256^3 2626, 2325; 384^3 8830, 8009; 170x145x141 525,
 // 506), below that blocks of 256 alone (128^3 298, 286, held 289; 128x128x90
-// 192, 191, held 203); float64 one of 192 or of a flat group (200^3 2439, 2322;
-// 192^3 2126, 2028; 320x320x200 6289, 5801), of 256 not (256^3 4786, held 4829);
-// the smaller sets two of 256 (D2Q33
-// 2000^2 204, 191, float64 398, 377; D3Q19 256^3 471, 446).  The cache prefers
-// many waves (64^3 FP32-shifted 30, held 49), and so does the adjoint's mix of
-// arithmetic and loads (128^3, 40 steps: 18.5 ms with and without).
+// 192, 191, held 203); float64 a flat group's block of 256 (200^3 2439, 2322) or
+// one of 192 (192^3 2126, 2028; 320x320x200 6289, 5801; 192x129x129 956, 932), no
+// other row (256^3 4786, held 4829; 128^3 591, 599; 64x250x250 1138, 1155; 64x251x251
+// 1141, 1435); the smaller sets two of 256 (D2Q33 2000^2 204, 191, float64 398,
+// 377; D3Q19 256^3 471, 446).  The cache prefers many waves (64^3 FP32-shifted 30,
+// held 49), and so does the adjoint's mix of arithmetic and loads (128^3, 40
+// steps: 18.5 ms with and without).
 void set_blocks(const lbm_ctx* ctx, KParams& k, BlockUse use) {
     const long long rows = static_cast<long long>(k.ny) * k.nz;
     const long long waves = k.flat ? (ctx->N + 63) / 64 : rows * ((k.nx + 63) / 64);
@@ -308,33 +360,30 @@ void set_blocks(const lbm_ctx* ctx, KParams& k, BlockUse use) {
     int most = lbm::step_max_threads(ctx->model, ctx->prec);
     int flat_most = lbm::flat_block_limit(ctx->Q, ctx->prec);
     int pack_most = use == kAdjoint ? lbm::kPackAdjMaxBlock : lbm::kPackMaxBlock;
-    k.resident = 0;
+    bool held = false;
+    double least = 1;   // blocks where they are
     if (few) {
         most = flat_most = pack_most = 64;
     } else if (k.nt && use != kAdjoint) {
-        if (ctx->Q >= 95 && use == kSteps) {
+        held = true;
+        if (ctx->Q >= 95 && !f64 && use == kStepsInPlace) {
+            held = pop_bytes(ctx) >= (size_t{1} << 30);
+            most = flat_most = held ? 128 : 256;
+        } else if (ctx->Q >= 95 || (ctx->Q >= 33 && !f64 && use == kSteps)) {
             flat_most = most;
-            k.resident = 1;
-        } else if (ctx->Q >= 95 && !f64) {
-            k.resident = pop_bytes(ctx) >= (size_t{1} << 30) ? 2 : 0;
-            most = flat_most = k.resident ? 128 : 256;
-        } else if (ctx->Q >= 95) {
-            flat_most = most;
-            k.resident = 1;
-        } else if (ctx->Q >= 33 && use == kSteps && !f64) {
-            flat_most = most;
-            k.resident = 1;
         } else {
             most = flat_most = 256;
-            k.resident = 2;
+            least = 2;
         }
     }
     k.rpb = 1;
+    double cells;   // of a block, on average
     if (k.flat) {
         // the waves of a group, in blocks of equal size
         const int group = (k.rg * k.nx + 63) / 64;
         k.chunks = (group + flat_most / 64 - 1) / (flat_most / 64);
         k.bx = (group + k.chunks - 1) / k.chunks * 64;
+        cells = static_cast<double>(k.nx) * k.ny / k.gpp / k.chunks;
     } else {
         // a held row that its blocks would leave a tenth short of lanes takes
         // larger ones (D3Q95 in place 192^3: 1115 us with 2 blocks of 128 a row,
@@ -344,21 +393,12 @@ void set_blocks(const lbm_ctx* ctx, KParams& k, BlockUse use) {
             return 10LL * r.chunks * r.bx > 11LL * k.nx;
         };
         int fit = most;
-        if (k.resident && short_of(most)) {
+        if (held && short_of(most)) {
             const int limit = lbm::step_max_threads(ctx->model, ctx->prec);
             while (fit < limit && short_of(fit)) fit += 64;
             if (short_of(fit)) fit = most;
         }
         const lbm::RowLaunch rl = lbm::row_launch(k.nx, rows, fit);
-        // 4 waves of D3Q95 a CU in place, 8 to 12 of the smaller sets (D3Q19
-        // 320x200x200 with 5 waves 427 us, 342 unlimited; D3Q15 384x200x200 with 6
-        // 354, 327)
-        if (k.resident && ctx->Q >= 95 && use == kStepsInPlace) {
-            if (f64) k.resident = rl.bx < 256 ? 1 : 0;
-            else if (rl.bx > 256) k.resident = 1;
-        } else if (k.resident && ctx->Q < 95) {
-            k.resident = (8 + rl.bx / 64 - 1) / (rl.bx / 64);
-        }
         k.chunks = rl.chunks;
         k.bx = rl.bx;
         if (lbm::kPackRows && k.nx % 64 == 0) {
@@ -368,7 +408,11 @@ void set_blocks(const lbm_ctx* ctx, KParams& k, BlockUse use) {
             while (k.nx * k.rpb * 2 <= maxb && rows % (k.rpb * 2) == 0) k.rpb *= 2;
             if (k.rpb > 1) k.bx = k.nx * k.rpb;   // else: the row launch above (chunks >= 1)
         }
+        cells = static_cast<double>(k.nx) * k.rpb / k.chunks;
+        if (ctx->Q >= 95 && f64 && use == kStepsInPlace) held = held && k.bx == 192;
     }
+    const double hold = held ? std::max(least, std::ceil(held_cells(ctx, use) / cells)) : 0.0;
+    k.resident = hold <= lbm::kMaxHeld ? static_cast<int>(hold) : 0;
     set_divisors(k);
     // D3Q95 steps of so few waves that even four times as many leave the CUs two
     // each: four share the work of one (k_step_split; us per step float64 64x8x8

@@ -66,3 +66,54 @@ def test_reserved_lds_holds_the_planned_number_of_blocks(plans, unit):
         assert 160 * 1024 // block == p["resident"], (case, p)
         got.add(p["resident"])
     assert len(got) >= 4, got
+
+
+# Cells in flight a held CU needs at least: fewer leave HBM idle (D3Q95
+# FP32-shifted 64x251x251 with one block of 64 cells 1308 us per step, unlimited 564).
+ENOUGH = {("D3Q95", "fp32s", "ab"): 300, ("D3Q95", "fp32s", "aa"): 230,
+          ("D3Q95", "fp64", "ab"): 150, ("D3Q95", "fp64", "aa"): 150,
+          ("D3Q15", "fp32s", "ab"): 600, ("D3Q15", "fp32s", "aa"): 600}
+
+
+def _enough(model, precision, streaming):
+    return ENOUGH.get((model, precision, streaming), 450 if precision == "fp32s" else 240)
+
+
+@pytest.mark.parametrize("model,extents", [
+    # odd row counts (rows do not pack), even ones, rows of one to many blocks, thin tubes
+    ("D3Q95", [(64, 251, 251), (64, 250, 251), (128, 129, 129), (192, 129, 129), (256, 129, 129),
+               (320, 111, 111), (400, 201, 201), (448, 161, 161), (11, 11, 20000), (5, 5, 60000),
+               (3, 3, 90000), (16, 11, 20000), (130, 131, 129), (100, 1, 40000)]),
+    ("D3Q19", [(64, 511, 511), (64, 512, 512), (128, 257, 257), (128, 256, 256), (192, 257, 257),
+               (400, 161, 161), (448, 161, 161), (5, 5, 200000), (11, 11, 90000)]),
+    ("D3Q15", [(64, 511, 511), (192, 257, 257), (384, 161, 161), (11, 11, 90000), (5, 7, 200000)]),
+    ("D2Q33", [(64, 100001), (128, 40001), (128, 100000), (192, 50001), (400, 30001),
+               (11, 500000), (2393, 3579)]),
+])
+@pytest.mark.parametrize("precision", ["fp64", "fp32s"])
+@pytest.mark.parametrize("streaming", ["ab", "aa"])
+def test_held_blocks_have_enough_cells(plans, model, extents, precision, streaming):
+    cases = [(model, e, precision, streaming) for e in extents]
+    held = 0
+    for (_, e, _, _), p in zip(cases, plans(cases)):
+        if p["resident"] == 0:
+            continue
+        held += 1
+        cells = 1
+        for n in e:
+            cells *= n
+        per_block = cells / p["blocks"]
+        need = _enough(model, precision, streaming)
+        assert p["resident"] * per_block >= need, (e, p)
+        assert p["resident"] <= 2 or (p["resident"] - 1) * per_block < need, (e, p)
+    assert held > 0
+
+
+def test_packed_rows_of_float64_in_place_are_not_held(plans):
+    # 128^3 held 599 us per step, unlimited 591; 64x250x250 1155, 1138; only a block of one
+    # row of 192 (or half of one of 320 or 384) gains
+    cases = [("D3Q95", e, "fp64", "aa") for e in ((128, 128, 128), (64, 250, 250), (64, 251, 251),
+                                                  (128, 129, 129), (256, 256, 256))]
+    assert [p["resident"] for p in plans(cases)] == [0] * len(cases)
+    cases = [("D3Q95", e, "fp64", "aa") for e in ((192, 192, 192), (320, 200, 200), (384, 150, 150))]
+    assert [p["resident"] for p in plans(cases)] == [1] * len(cases)

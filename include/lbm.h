@@ -258,9 +258,9 @@ int lbm_get_populations(lbm_ctx* ctx, double* f);
  * lbm_step - advance n >= 0 time steps of the update rule.  Each step is one
  * kernel: gather f_i(x, t + 1) = f*_i(x - e_i, t) (periodic, any extent),
  * moments, 4th-order equilibrium, BGK relaxation, coalesced store of
- * f*(x, t + 1).  Narrow 2D grids (up to about 16 cells across and a few
- * thousand in all, two buffers) take up to 7 steps of a call in one kernel,
- * with the same results bit for bit.  An even number of steps leaves the state
+ * f*(x, t + 1).  Narrow 2D grids (two buffers) take up to 7 steps of a call in
+ * one kernel where that is expected to be faster (up to about 20 cells across in
+ * float64, 36 in FP32-shifted), with the same results bit for bit.  An even number of steps leaves the state
  * in the buffer it was in, an odd number in the other one.  Asynchronous.
  */
 int lbm_step(lbm_ctx* ctx, int n);

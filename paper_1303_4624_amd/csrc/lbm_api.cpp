@@ -423,14 +423,33 @@ void set_blocks(const lbm_ctx* ctx, KParams& k, BlockUse use) {
 }
 
 // Strips of a narrow 2D grid (k_steps_strip): steps per launch and strip width
-// by the time they are expected to take.  A launch costs about `fixed` us
-// beside its steps, a step of a block `wave` us while it has one wave per SIMD
-// and `two` with two (measured: D2Q33 float64 128x4, 7 steps of strips of 4:
-// 2.9 us per step, 5x1500 in strips of 16 3.4, 300x12 5 steps 3.7, 11x800 held 5
-// steps 4.0; FP32-shifted 128x4 2.5, 11x800 3.6).  Single steps take about
-// `single` (the same grids: 4.2-5.0, 4.9, 3.9, 5.0; 4.3, 5.1), so strips are
-// taken where they promise a tenth less: up to about 16 cells across.  All
-// blocks run at once (one per CU, the strip's LDS).
+// by the time they are expected to take on the GPU.  A launch costs `launch` us and
+// `gather` for every 1000 cells its first step reads (of the difference between
+// plans of one grid a quarter: their reads overlap in the caches), a step of a
+// block `step` and `wave` for each wave that works in it; in strips along x the
+// lanes of a wave lie in different rows, which costs the first load and the last
+// store `lines` per wave and row.  Single steps take `one` and `cells` for every
+// 1000 cells.  Fitted to 2700 plans of 53 grids of 150 to 38000 cells, 1 to 42
+// across, timed behind a full queue: 7 % RMS.  A host that launches steps one by
+// one adds to them (3.8 to 5.2 us a launch on the hosts measured), so strips are
+// also taken where they promise up to 0.1 (FP32-shifted 0.2, along x 0.3) us more
+// (130x14: single 3.9, from the host 4.8, strips 4.0); along rows that are not
+// flat, where the fit is worst, they have to promise 0.3 less.  Held ends that lie
+// across the lanes of a wave (strips along x) make single steps faster (300x12
+// 3.9, strips 4.9).  All blocks run at once (one per CU, the strip's LDS).
+// us per step behind a full queue, single and in the strips taken (steps of
+// cells), float64 and FP32-shifted:
+//   128x4         4.21, 2.91 (6 of 8)   4.29, 2.43 (6 of 8)
+//   5x1500        3.95, 3.02 (6 of 8)   3.77, 2.70 (6 of 8)
+//   11x800 held   5.02, 3.99 (4 of 4)   5.09, 3.55 (4 of 4)
+//   300x12        3.90, 3.76 (5 of 4)   3.78, 3.57 (5 of 4)
+//   600x10        4.40, 4.15 (5 of 4)   4.33, 3.67 (5 of 4)
+//   16x2400       5.51, 5.23 (3 of 12)  4.62, 4.33 (3 of 12)
+//   8x8192        6.96, 4.69 (5 of 32)  5.23, 3.97 (5 of 32)
+//   20x800 held   5.08, 4.87 (3 of 4)   5.01, 4.00 (3 of 4)
+//   25x800 held   5.31 (strips 5.08)    5.18, 4.49 (3 of 4)
+//   40x900        5.50 (strips 5.83)    4.43 (strips 5.24)
+//   256x20        4.30 (strips 5.80)    4.31 (strips 5.13)
 void strip_plan(lbm_ctx* ctx) {
     KParams& k = ctx->kp;
     lbm::StripParams& sp = k.strip;
@@ -438,16 +457,22 @@ void strip_plan(lbm_ctx* ctx) {
     sp = lbm::StripParams{};
     sp.steps = 1;
     if (ctx->D != 2 || ctx->aa) return;
-    const bool f64 = ctx->prec == Prec::F64;
-    const double fixed = f64 ? 1.6 : 1.4, wave = f64 ? 2.6 : 2.2, two = f64 ? 4.2 : 3.4,
-                 single = f64 ? 4.4 : 4.2;
+    const bool f64 = ctx->prec == Prec::F64, held = k.hold_lo + k.hold_hi > 0;
+    const double launch = f64 ? 2.4 : 1.6, gather = f64 ? 0.049 : 0.034, wave = f64 ? 0.20 : 0.14,
+                 lines = f64 ? 0.023 : 0.028,
+                 step = (f64 ? 1.80 : 1.87) + (held ? f64 ? 0.39 : 0.53 : 0.0);
     const int reach = lbm::model_reach(ctx->model);
     sp.along_y = k.ny >= k.nx;
     sp.n = sp.along_y ? k.ny : k.nx;
     sp.s = sp.along_y ? k.nx : k.ny;
-    if (sp.s > lbm::kStripCells) return;
-    double best = 0.9 * single;
-    for (int steps : {7, 5, 3, 2}) {
+    if (sp.s > lbm::kStripCells || (held && !sp.along_y)) return;
+    const double cells = (f64 ? 0.036 : 0.014) + (k.flat ? 0.0 : f64 ? 0.04 : 0.01),
+                 one = (f64 ? 3.8 : 3.75) + (held ? f64 ? 0.9 : 1.1 : 0.0) +
+                       (k.flat ? 0.0 : f64 ? 0.2 : 0.45) + cells * ctx->N / 1000;
+    const double more = !sp.along_y ? (k.flat ? 0.3 : -0.3) : f64 ? 0.1 : 0.2;
+    const auto waves = [&](int len) { return (len * sp.s + 63) / 64; };
+    double best = std::numeric_limits<double>::infinity(), taken = best;
+    for (int steps = 7; steps >= 2; --steps) {
         for (int w = reach; w <= lbm::kStripCells; w += reach) {
             const int margin = reach * (steps - 1);
             const bool whole = w + 2 * margin >= sp.n;
@@ -455,18 +480,22 @@ void strip_plan(lbm_ctx* ctx) {
             if (static_cast<long long>(len) * sp.s > lbm::kStripCells) break;
             const int blocks = whole ? 1 : (sp.n + w - 1) / w;
             if (blocks > lbm::kCUs) continue;
-            double us = fixed;
-            for (int t = 0; t < steps; ++t)
-                us += ((whole ? len : len - 2 * reach * t) * sp.s > 256) ? two : wave;
+            const int lost = whole ? 0 : 2 * reach;   // cells along the strip, per step
+            const double reads = gather * blocks * len * sp.s / 1000;
+            double us = launch + step * steps + reads / 4;
+            for (int t = 0; t < steps; ++t) us += wave * waves(len - lost * t);
+            if (!sp.along_y) us += lines * sp.s * (waves(len) + waves(len - lost * (steps - 1)));
             if (us / steps < best) {
                 best = us / steps;
+                taken = (us + 0.75 * reads) / steps;
                 sp.steps = steps;
                 sp.w = whole ? sp.n : w;
-                sp.threads = (len * sp.s + 63) / 64 * 64;
+                sp.threads = waves(len) * 64;
             }
             if (whole) break;
         }
     }
+    if (!(taken < one + more)) sp.steps = 1;
     sp.by_s = fast_div(sp.s);
     sp.inv_s = 65536u / static_cast<unsigned>(sp.s) + 1;
     sp.inv_n = 65536u / static_cast<unsigned>(sp.n) + 1;
@@ -994,6 +1023,7 @@ LBM_API int lbm_set_fixed_planes(lbm_ctx* ctx, int n_lo, int n_hi, const double*
     ctx->kp.hold_hi = n_hi;
     ctx->kp.hold[0] = fs[0];
     ctx->kp.hold[1] = fs[1];
+    strip_plan(ctx);
     drop_graph(ctx);
     return LBM_OK;
 }

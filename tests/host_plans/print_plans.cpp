@@ -1,5 +1,5 @@
 // Prints the launch plan the library chooses for each grid read from stdin
-// ("D Q nx ny nz precision streaming"), one line of name=value pairs per grid.
+// ("D Q nx ny nz precision streaming hold", hold planes at either end), one line of name=value pairs per grid.
 // The plans are host arithmetic: the kernel launchers are the stubs of
 // tests/sanitize/launcher_stubs.cpp.
 #include "lbm_api.cpp"
@@ -8,18 +8,20 @@
 #include <cstdio>
 
 int main() {
-    int D, Q, precision, streaming;
+    int D, Q, precision, streaming, hold;
     int64_t ext[3];
-    while (std::scanf("%d %d %" SCNd64 " %" SCNd64 " %" SCNd64 " %d %d", &D, &Q, &ext[0], &ext[1],
-                      &ext[2], &precision, &streaming) == 7) {
+    while (std::scanf("%d %d %" SCNd64 " %" SCNd64 " %" SCNd64 " %d %d %d", &D, &Q, &ext[0], &ext[1],
+                      &ext[2], &precision, &streaming, &hold) == 8) {
         std::vector<int32_t> e(static_cast<size_t>(Q) * D);
         std::vector<double> w(Q);
         double c = 0;
+        const double end[] = {1.0, 0.0, 0.0, 0.5, 0.5};   // (rho, U, T), T > 0 in 2D and 3D
         lbm_ctx* ctx = nullptr;
         if (lbm_velocity_set(D, Q, e.data(), w.data(), &c) != LBM_OK ||
             lbm_create(&ctx, D, Q, e.data(), w.data(), c, ext, 1.3, precision, 1.0, nullptr) !=
                 LBM_OK ||
-            lbm_set_streaming(ctx, streaming) != LBM_OK) {
+            lbm_set_streaming(ctx, streaming) != LBM_OK ||
+            lbm_set_fixed_planes(ctx, hold, hold, end, end) != LBM_OK) {
             std::printf("error=%s\n", lbm_last_error(ctx));
             continue;
         }

@@ -29,13 +29,14 @@ def plans(tmp_path_factory):
     assert res.returncode == 0, res.stdout[-4000:]
 
     def ask(cases):
-        """cases: (model, extent, precision, streaming); one dict of ints each."""
+        """cases: (model, extent, precision, streaming[, planes held at either end]);
+        one dict of ints each."""
         lines = []
-        for model, extent, precision, streaming in cases:
+        for model, extent, precision, streaming, *hold in cases:
             ext = list(extent) + [1] * (3 - len(extent))
             lines.append(" ".join(str(x) for x in (
                 len(extent), Q[model], *ext, {"fp64": 0, "fp32s": 1}[precision],
-                {"ab": 0, "aa": 1}[streaming])))
+                {"ab": 0, "aa": 1}[streaming], *(hold or [0]))))
         run = subprocess.run([exe], input="\n".join(lines) + "\n", stdout=subprocess.PIPE,
                              text=True, timeout=300)
         assert run.returncode == 0
@@ -117,3 +118,31 @@ def test_packed_rows_of_float64_in_place_are_not_held(plans):
     assert [p["resident"] for p in plans(cases)] == [0] * len(cases)
     cases = [("D3Q95", e, "fp64", "aa") for e in ((192, 192, 192), (320, 200, 200), (384, 150, 150))]
     assert [p["resident"] for p in plans(cases)] == [1] * len(cases)
+
+
+# Narrow 2D grids: (extent, held) where several steps per launch were measured faster than
+# single steps, and where they were slower, behind a full queue and from the host.
+STRIPS = {
+    "fp64": [((128, 4), 0), ((11, 800), 4), ((5, 1500), 0), ((16, 2400), 4), ((20, 800), 4),
+             ((8, 2400), 4), ((600, 10), 0), ((3, 4000), 0), ((1, 500), 0)],
+    "fp32s": [((128, 4), 0), ((11, 800), 4), ((5, 1500), 0), ((16, 2400), 4), ((20, 800), 4),
+              ((25, 800), 4), ((36, 500), 4), ((300, 12), 0), ((600, 10), 0), ((3, 4000), 0)],
+}
+SINGLE = {
+    "fp64": [((400, 16), 0), ((400, 16), 4), ((900, 20), 0), ((256, 20), 0), ((300, 12), 4),
+             ((1000, 14), 4), ((40, 900), 0), ((60, 30), 0), ((64, 64), 0)],
+    "fp32s": [((900, 20), 0), ((900, 16), 4), ((400, 16), 4), ((256, 20), 0), ((300, 12), 4),
+              ((40, 900), 0), ((46, 42), 0), ((60, 30), 0), ((378, 24), 0), ((1423, 24), 0)],
+}
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32s"])
+def test_strips_are_taken_where_they_are_faster(plans, precision):
+    got = plans([("D2Q33", e, precision, "ab", h) for e, h in STRIPS[precision]])
+    for (e, h), p in zip(STRIPS[precision], got):
+        assert p["strip_steps"] > 1 and 64 <= p["strip_threads"] <= 512, (e, h, p)
+    got = plans([("D2Q33", e, precision, "ab", h) for e, h in SINGLE[precision]])
+    for (e, h), p in zip(SINGLE[precision], got):
+        assert p["strip_steps"] == 1, (e, h, p)
+    assert all(p["strip_steps"] == 1 for p in plans(
+        [("D2Q33", e, precision, "aa", h) for e, h in STRIPS[precision]]))

@@ -146,3 +146,10 @@ def test_strips_are_taken_where_they_are_faster(plans, precision):
         assert p["strip_steps"] == 1, (e, h, p)
     assert all(p["strip_steps"] == 1 for p in plans(
         [("D2Q33", e, precision, "aa", h) for e, h in STRIPS[precision]]))
+
+
+def test_wide_strips_of_the_gpu_test_are_planned(plans):
+    from test_gpu_strips_wide import WIDE
+    cases = [("D2Q33", e, p, "ab", h) for p, grids in WIDE.items() for e, h in grids]
+    for case, p in zip(cases, plans(cases)):
+        assert p["strip_steps"] > 1 and p["strip_threads"] > 256, (case, p)

@@ -153,3 +153,12 @@ def test_wide_strips_of_the_gpu_test_are_planned(plans):
     cases = [("D2Q33", e, p, "ab", h) for p, grids in WIDE.items() for e, h in grids]
     for case, p in zip(cases, plans(cases)):
         assert p["strip_steps"] > 1 and p["strip_threads"] > 256, (case, p)
+
+
+@pytest.mark.parametrize("streaming", ["ab", "aa"])
+def test_block_order_switches_on_the_grids_of_the_gpu_test(plans, streaming):
+    from test_gpu_tune_blocks import ORDERED
+    cases = [(m, e, p, streaming) for m, e, p, _, _ in ORDERED]
+    for (m, e, _, flat, packed), p in zip(ORDERED, plans(cases)):
+        assert p["order"] == 1, (m, e, p)
+        assert (p["flat"] == 1) == flat and (p["rpb"] > 1) == packed, (m, e, p)

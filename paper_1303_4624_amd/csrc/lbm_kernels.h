@@ -1323,13 +1323,17 @@ __device__ __forceinline__ R eq_pd(R c0, R c1, R c2, R s) {
 // i.e. the invariant <lambda^{t+1}, f^{t+1}> of the step's homogeneity.
 // The MARK instances (one step per checkpoint segment) hold the mark's loads
 // as well and may use up to 256 registers (2 waves per SIMD instead of 3) to
-// avoid spilling.
+// avoid spilling; so may the FLAT ones (177), whose lane mapping gains more than
+// the third wave (us per recomputed step and transposed step together, against
+// padded rows with 3 waves: D3Q95 FP32-shifted 100x75x50 147, 115; 150x150x100
+// 736, 585; 11x11x800 held 63, 27; 200x60x60 232, 203).  By rows the third wave is
+// worth 5 to 8 % (held 64x64x128 129 against 139 us, 128x128x100 379 against 398).
 // HOLD: the post-collision values of cells on held planes are constants, so
 // their adjoint state is zero (the cells are computed like the others and
 // their output replaced, keeping every wave on the same barriers).
 template <class M, class P, bool FLAT, bool NT, bool COLLIDE, bool MARK, bool HOLD>
 __global__ __launch_bounds__(row_block_limit(M::Q, P::id))
-__attribute__((amdgpu_waves_per_eu(MARK || FLAT || HOLD ? (P::adj_waves < 2 ? P::adj_waves : 2) : P::adj_waves)))
+__attribute__((amdgpu_waves_per_eu(MARK || FLAT ? (P::adj_waves < 2 ? P::adj_waves : 2) : P::adj_waves)))
 void k_adjoint(const typename P::S* __restrict__ lsrc, typename P::S* __restrict__ ldst,
                const typename P::S* __restrict__ mom, KParams k, double* __restrict__ partA,
                const typename P::S* __restrict__ mark_state, double* __restrict__ partM) {
@@ -1342,6 +1346,10 @@ void k_adjoint(const typename P::S* __restrict__ lsrc, typename P::S* __restrict
     // by rows, surplus lanes repeat the store of the row's last cell: one
     // register less than filling its line, which keeps 3 waves per SIMD
     if constexpr (!FLAT) cl.at = cl.x;
+    // x of a wave's first lane less its thread index, uniform (HOLD by rows)
+    int x0 = 0;
+    if constexpr (HOLD && !FLAT)
+        x0 = __builtin_amdgcn_readfirstlane(cl.x - static_cast<int>(threadIdx.x));
 
     S mu[Q];
     gather<M, -1, FLAT>(lsrc, k, cl, mu);
@@ -1451,6 +1459,13 @@ void k_adjoint(const typename P::S* __restrict__ lsrc, typename P::S* __restrict
     const R ge = R(w * at * invr * (1.0 / D));
     const R gr = R(w * grho);
     const R omc = R(k.omc);
+    if constexpr (HOLD && !FLAT) {
+        // formed again from the thread index: the register it would be kept in
+        // is the one too many for 3 waves
+        asm volatile("" : "+s"(x0));
+        const int x = static_cast<int>(threadIdx.x) + x0;
+        cl.at = x < k.nx ? x : k.nx - 1;
+    }
     PlaneWriter<S, FLAT, NT> out_w(ldst, k, cl);
     bool held = false;
     if constexpr (HOLD) {

@@ -1090,6 +1090,29 @@ __global__ __launch_bounds__(kBlock) void k_init(const double* __restrict__ rho,
                           T[c]);
 }
 
+// Moves Q values of a cell, load(I) to store(I, value), in batches: all loads of a
+// batch are in flight before its first store.  Left to itself the compiler may
+// wait for each load at its store (get_populations float64 D3Q95 33x34x26: 27 us
+// against 11.2 in batches of 24, 11.6 of 48; 96x48x21 31, 25; 64^3 86, 78).
+template <int Q, class S, class Load, class Store>
+__device__ __forceinline__ void copy_cell(Load&& load, Store&& store) {
+    constexpr int batch = 24;
+    static_for<(Q + batch - 1) / batch>([&](auto BI) {
+        constexpr int first = decltype(BI)::value * batch;
+        constexpr int n = Q - first < batch ? Q - first : batch;
+        S v[n];
+        static_for<n>([&](auto J) {
+            constexpr int j = decltype(J)::value;
+            v[j] = load(std::integral_constant<int, first + j>{});
+        });
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<n>([&](auto J) {
+            constexpr int j = decltype(J)::value;
+            store(std::integral_constant<int, first + j>{}, v[j]);
+        });
+    });
+}
+
 // Copy float64 f[Q][N] into storage, and back.
 template <class M, class P, int FORM>
 __global__ __launch_bounds__(kBlock) void k_set_pop(const double* __restrict__ fin,
@@ -1097,15 +1120,16 @@ __global__ __launch_bounds__(kBlock) void k_set_pop(const double* __restrict__ f
     const long long c = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (c >= k.N) return;
     const PopAt<M, FORM> pa(k, c);
-    static_for<M::Q>([&](auto I) {
-        constexpr int i = decltype(I)::value;
-        constexpr int g = M::table.group[i];
-        const double val = fin[static_cast<long long>(i) * k.N + c];
-        if constexpr (P::shifted)
-            f[pa.template at<i>()] = static_cast<float>(val - k.W[g] * k.rho0);
-        else
-            f[pa.template at<i>()] = val;
-    });
+    copy_cell<M::Q, double>(
+        [&](auto I) { return fin[static_cast<long long>(decltype(I)::value) * k.N + c]; },
+        [&](auto I, double val) {
+            constexpr int i = decltype(I)::value;
+            constexpr int g = M::table.group[i];
+            if constexpr (P::shifted)
+                f[pa.template at<i>()] = static_cast<float>(val - k.W[g] * k.rho0);
+            else
+                f[pa.template at<i>()] = val;
+        });
 }
 
 template <class M, class P, int FORM>
@@ -1114,12 +1138,14 @@ __global__ __launch_bounds__(kBlock) void k_get_pop(const typename P::S* __restr
     const long long c = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (c >= k.N) return;
     const PopAt<M, FORM> pa(k, c);
-    static_for<M::Q>([&](auto I) {
-        constexpr int i = decltype(I)::value;
-        constexpr int g = M::table.group[i];
-        const double val = static_cast<double>(f[pa.template at<i>()]);
-        fout[static_cast<long long>(i) * k.N + c] = P::shifted ? val + k.W[g] * k.rho0 : val;
-    });
+    copy_cell<M::Q, typename P::S>(
+        [&](auto I) { return f[pa.template at<decltype(I)::value>()]; },
+        [&](auto I, typename P::S v) {
+            constexpr int i = decltype(I)::value;
+            constexpr int g = M::table.group[i];
+            const double val = static_cast<double>(v);
+            fout[static_cast<long long>(i) * k.N + c] = P::shifted ? val + k.W[g] * k.rho0 : val;
+        });
 }
 
 // Copy of a stored state in form FORM into the two-buffer form (same
@@ -1131,10 +1157,9 @@ __global__ __launch_bounds__(kBlock) void k_to_ab(const typename P::S* __restric
     if (c >= k.N) return;
     const PopAt<M, FORM> src(k, c);
     const PopAt<M, kFormAB> dst(k, c);
-    static_for<M::Q>([&](auto I) {
-        constexpr int i = decltype(I)::value;
-        out[dst.template at<i>()] = f[src.template at<i>()];
-    });
+    copy_cell<M::Q, typename P::S>(
+        [&](auto I) { return f[src.template at<decltype(I)::value>()]; },
+        [&](auto I, typename P::S val) { out[dst.template at<decltype(I)::value>()] = val; });
 }
 
 // The reverse: a state in the two-buffer form copied into form FORM.
@@ -1145,10 +1170,9 @@ __global__ __launch_bounds__(kBlock) void k_from_ab(const typename P::S* __restr
     if (c >= k.N) return;
     const PopAt<M, kFormAB> src(k, c);
     const PopAt<M, FORM> dst(k, c);
-    static_for<M::Q>([&](auto I) {
-        constexpr int i = decltype(I)::value;
-        out[dst.template at<i>()] = f[src.template at<i>()];
-    });
+    copy_cell<M::Q, typename P::S>(
+        [&](auto I) { return f[src.template at<decltype(I)::value>()]; },
+        [&](auto I, typename P::S val) { out[dst.template at<decltype(I)::value>()] = val; });
 }
 
 // Raw float64 sums of one cell: sum v, sum v e, sum v |e|^2 of the stored values.

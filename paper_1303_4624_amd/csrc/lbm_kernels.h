@@ -1090,13 +1090,15 @@ __global__ __launch_bounds__(kBlock) void k_init(const double* __restrict__ rho,
                           T[c]);
 }
 
-// Moves Q values of a cell, load(I) to store(I, value), in batches: all loads of a
-// batch are in flight before its first store.  Left to itself the compiler may
-// wait for each load at its store (get_populations float64 D3Q95 33x34x26: 27 us
-// against 11.2 in batches of 24, 11.6 of 48; 96x48x21 31, 25; 64^3 86, 78).
+// Moves Q values of a cell, load(I) to store(I, value); doubles in batches: all
+// loads of a batch are in flight before its first store.  Left to itself the
+// compiler may wait for each load at its store (get_populations float64 D3Q95
+// 33x34x26: 27 us against 11.2 in batches of 24, 11.6 of 48; 96x48x21 31, 25; 64^3
+// 86, 78).  Its order is the better one for floats (64^3 51.9 us, in batches 54.4;
+// D2Q33 1024^2 86.2, 89.7).
 template <int Q, class S, class Load, class Store>
 __device__ __forceinline__ void copy_cell(Load&& load, Store&& store) {
-    constexpr int batch = 24;
+    constexpr int batch = sizeof(S) == 8 ? 24 : 1;
     static_for<(Q + batch - 1) / batch>([&](auto BI) {
         constexpr int first = decltype(BI)::value * batch;
         constexpr int n = Q - first < batch ? Q - first : batch;
@@ -1105,7 +1107,7 @@ __device__ __forceinline__ void copy_cell(Load&& load, Store&& store) {
             constexpr int j = decltype(J)::value;
             v[j] = load(std::integral_constant<int, first + j>{});
         });
-        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (sizeof(S) == 8) __builtin_amdgcn_sched_barrier(0);
         static_for<n>([&](auto J) {
             constexpr int j = decltype(J)::value;
             store(std::integral_constant<int, first + j>{}, v[j]);

@@ -1078,13 +1078,34 @@ __global__ __launch_bounds__(kStripCells) void k_steps_strip(
 }
 
 // ---------------------------------------------------------------------------
+// Cell of a thread of the kernels that fill or copy a state, one cell each.
+// A population run holds up to 1024 cells or more, four blocks' worth, and
+// blocks go to the 8 XCDs in turn: neighbouring pieces of a run would be
+// written from four L2s at once.  Where it matters (the 4th-order sets, when they
+// write from fields, in float64 also when they copy) each XCD takes a contiguous
+// range of blocks (us, in turn against contiguous: D3Q95 float64 init 96x192x162
+// 509, 448, 128x128x100 266, 246; set_populations 940, 867, 510, 474; restore in
+// place 949, 835; D2Q33 FP32-shifted 3000^2 set_populations 739, 690).  The smaller
+// sets and the reads of the FP32-shifted storage lose (D3Q19 200^3 init 164, 172;
+// D3Q95 256x256x128 get_populations 1809, 1828).
+template <class M, class P, bool FILL>
+__device__ __forceinline__ long long cell_of_thread() {
+    long long b = blockIdx.x;
+    if constexpr (LBM_XCD_REMAP && M::Q >= 33 && (FILL || !P::shifted)) {
+        const int nb = gridDim.x, xcd = blockIdx.x & 7, pos = blockIdx.x >> 3, q = nb >> 3,
+                  r = nb & 7;
+        b = (xcd < r) ? xcd * (q + 1) + pos : r * (q + 1) + (xcd - r) * q + pos;
+    }
+    return b * blockDim.x + threadIdx.x;
+}
+
 // f = f^eq(rho, U, T) from float64 fields.
 template <class M, class P, int FORM>
 __global__ __launch_bounds__(kBlock) void k_init(const double* __restrict__ rho,
                                                  const double* __restrict__ U,
                                                  const double* __restrict__ T,
                                                  typename P::S* __restrict__ f, KParams k) {
-    const long long c = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
+    const long long c = cell_of_thread<M, P, true>();
     if (c >= k.N) return;
     store_feq<M, P, FORM>(f, k, c, rho[c], U[c], U[k.N + c], (M::D == 3) ? U[2 * k.N + c] : 0.0,
                           T[c]);
@@ -1119,7 +1140,7 @@ __device__ __forceinline__ void copy_cell(Load&& load, Store&& store) {
 template <class M, class P, int FORM>
 __global__ __launch_bounds__(kBlock) void k_set_pop(const double* __restrict__ fin,
                                                     typename P::S* __restrict__ f, KParams k) {
-    const long long c = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
+    const long long c = cell_of_thread<M, P, true>();
     if (c >= k.N) return;
     const PopAt<M, FORM> pa(k, c);
     copy_cell<M::Q, double>(
@@ -1137,7 +1158,7 @@ __global__ __launch_bounds__(kBlock) void k_set_pop(const double* __restrict__ f
 template <class M, class P, int FORM>
 __global__ __launch_bounds__(kBlock) void k_get_pop(const typename P::S* __restrict__ f,
                                                     double* __restrict__ fout, KParams k) {
-    const long long c = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
+    const long long c = cell_of_thread<M, P, false>();
     if (c >= k.N) return;
     const PopAt<M, FORM> pa(k, c);
     copy_cell<M::Q, typename P::S>(
@@ -1155,7 +1176,7 @@ __global__ __launch_bounds__(kBlock) void k_get_pop(const typename P::S* __restr
 template <class M, class P, int FORM>
 __global__ __launch_bounds__(kBlock) void k_to_ab(const typename P::S* __restrict__ f,
                                                   typename P::S* __restrict__ out, KParams k) {
-    const long long c = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
+    const long long c = cell_of_thread<M, P, false>();
     if (c >= k.N) return;
     const PopAt<M, FORM> src(k, c);
     const PopAt<M, kFormAB> dst(k, c);
@@ -1168,7 +1189,7 @@ __global__ __launch_bounds__(kBlock) void k_to_ab(const typename P::S* __restric
 template <class M, class P, int FORM>
 __global__ __launch_bounds__(kBlock) void k_from_ab(const typename P::S* __restrict__ f,
                                                     typename P::S* __restrict__ out, KParams k) {
-    const long long c = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
+    const long long c = cell_of_thread<M, P, false>();
     if (c >= k.N) return;
     const PopAt<M, kFormAB> src(k, c);
     const PopAt<M, FORM> dst(k, c);

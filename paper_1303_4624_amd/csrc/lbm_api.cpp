@@ -276,6 +276,9 @@ void set_divisors(KParams& k) {
 // Kernels that share a block size.
 enum BlockUse { kSteps, kStepsInPlace, kAdjoint };
 
+// FP32-shifted D3Q95 states from which both in-place steps are held (see set_blocks).
+constexpr size_t kHeldInPlace = size_t{1} << 30;
+
 // Cells that the blocks a CU holds at once have together at least, where they are
 // held (see set_blocks).  Cells and not blocks are counted, since a short row or
 // a thin plane may give a block only a few.  us per step by blocks per CU (- not
@@ -322,7 +325,10 @@ enum BlockUse { kSteps, kStepsInPlace, kAdjoint };
 //     D3Q15 256x200x200   256   506 *415  417  420  422    -  423
 int held_cells(const lbm_ctx* ctx, BlockUse use) {
     const bool f64 = ctx->prec == Prec::F64;
-    if (ctx->Q >= 95) return f64 ? 150 : use == kStepsInPlace ? 230 : 300;
+    if (ctx->Q >= 95) {
+        if (f64) return 150;
+        return use == kStepsInPlace && pop_bytes(ctx) >= kHeldInPlace ? 230 : 300;
+    }
     return f64 ? 240 : ctx->Q >= 19 ? 450 : 600;
 }
 
@@ -343,14 +349,18 @@ int held_cells(const lbm_ctx* ctx, BlockUse use) {
 // FP32-shifted one of 512 (2393x3579 403, 388; 8192^2 2914, 2867), float64 two of
 // 256 (814, 788); D3Q19 FP32-shifted two of 256 (256^3 438, 416), float64 the same
 // (889, 856).
-// In place the writes hit lines other blocks read: D3Q95 FP32-shifted two
-// blocks of 128 from 1 GB (256^3 2626, 2325; 384^3 8830, 8009; 170x145x141 525,
-// 506), below that blocks of 256 alone (128^3 298, 286, held 289; 128x128x90
-// 192, 191, held 203); float64 a flat group's block of 256 (200^3 2439, 2322) or
-// one of 192 (192^3 2126, 2028; 320x320x200 6289, 5801; 192x129x129 956, 932), no
-// other row (256^3 4786, held 4829; 128^3 591, 599; 64x250x250 1138, 1155; 64x251x251
-// 1141, 1435); the smaller sets two of 256 (D2Q33 2000^2 204, 191, float64 398,
-// 377; D3Q19 256^3 471, 446).  The cache prefers many waves (64^3 FP32-shifted 30,
+// In place the two steps differ (see k_step_aa): the one that pushes writes lines
+// other blocks read and is held; the local one touches its own cells only.  us
+// per step (the mean of both), unlimited, push held, both held: D3Q95 float64
+// 192x70x60 218, 210, 228; 256x64x80 357, 353, 374; 128^3 588, 586, 600; 400x100x100
+// 1249, 1189, 1172; 512x100x100 1507, 1469, 1482; flat 150x100x60 250, 241, 254; 200x100x100
+// 606, 579, 586; rows of one block of 192, or of two, both from 1.5 GB (192x128x100
+// 741, 713, 711; 320x100x100 994, 942, 922; below 384x60x44 293, 277, 292); FP32-shifted
+// below 1 GB 57x176x86 136, 126, 126; 300x80x60 194, 187, 200; 128^3 271, 269, 281;
+// 320x80x60 227, 219, 220; from 1 GB two blocks of 128 in both (256x128x128 647, 597,
+// 588; 384^3 8830, -, 8009; 170x145x141 525, -, 506).  The smaller sets two blocks of 256
+// in both (D2Q33 2000^2 179, 168, 163, float64 365, 356, 345; D3Q19 float64
+// 200x150x110 165, 157, 155).  The cache prefers many waves (64^3 FP32-shifted 30,
 // held 49), and so does the adjoint's mix of arithmetic and loads (128^3, 40
 // steps: 18.5 ms with and without).
 void set_blocks(const lbm_ctx* ctx, KParams& k, BlockUse use) {
@@ -367,8 +377,7 @@ void set_blocks(const lbm_ctx* ctx, KParams& k, BlockUse use) {
     } else if (k.nt && use != kAdjoint) {
         held = true;
         if (ctx->Q >= 95 && !f64 && use == kStepsInPlace) {
-            held = pop_bytes(ctx) >= (size_t{1} << 30);
-            most = flat_most = held ? 128 : 256;
+            most = flat_most = pop_bytes(ctx) >= kHeldInPlace ? 128 : 256;
         } else if (ctx->Q >= 95 || (ctx->Q >= 33 && !f64 && use == kSteps)) {
             flat_most = most;
         } else {
@@ -409,10 +418,16 @@ void set_blocks(const lbm_ctx* ctx, KParams& k, BlockUse use) {
             if (k.rpb > 1) k.bx = k.nx * k.rpb;   // else: the row launch above (chunks >= 1)
         }
         cells = static_cast<double>(k.nx) * k.rpb / k.chunks;
-        if (ctx->Q >= 95 && f64 && use == kStepsInPlace) held = held && k.bx == 192;
     }
     const double hold = held ? std::max(least, std::ceil(held_cells(ctx, use) / cells)) : 0.0;
     k.resident = hold <= lbm::kMaxHeld ? static_cast<int>(hold) : 0;
+    k.resident_local = k.resident;
+    if (ctx->Q >= 95 && use == kStepsInPlace) {
+        const size_t bytes = pop_bytes(ctx);
+        const bool local = f64 ? !k.flat && k.bx == 192 && 2 * bytes >= 3 * kHeldInPlace
+                               : bytes >= kHeldInPlace;
+        if (!local) k.resident_local = 0;
+    }
     set_divisors(k);
     // D3Q95 steps of so few waves that even four times as many leave the CUs two
     // each: four share the work of one (k_step_split; us per step float64 64x8x8

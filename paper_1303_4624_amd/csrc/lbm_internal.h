@@ -160,6 +160,7 @@ struct KParams {
     int bx;                   // threads per block (multiple of 64)
     int split;                // 1: kSplit blocks share the cells of one (two buffers)
     int resident;             // blocks a CU holds at once (0: as many as fit)
+    int resident_local;       // the same of the in-place step that stores to its own cells
     FastDiv by_nx, by_ny, by_gpp, by_chunks;
     unsigned inv_nx, inv_ny, inv_nz;   // 65536 / n + 1 (axes of at most kMaxDisp cells)
     int reverse;              // 1: this launch takes the blocks from the last to the first

@@ -1734,7 +1734,8 @@ hipError_t ModelKernels<M, PR>::step_aa(const KParams& kp, void* f, bool push, v
     using S = typename P::S;
     const dim3 grid(static_cast<unsigned>(step_blocks(M::id, PR, kp)));
     const auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, grid, dim3(kp.bx), limit_blocks(kernel, kp.resident), s,
+        hipLaunchKernelGGL(kernel, grid, dim3(kp.bx),
+                           limit_blocks(kernel, push ? kp.resident : kp.resident_local), s,
                            static_cast<S*>(f), kp,
                            static_cast<S*>(mom_out));
     };

@@ -28,10 +28,10 @@ int main() {
         const KParams& k = ctx->kp;
         const long long blocks = lbm::step_blocks(ctx->model, ctx->prec, k);
         const int chunk = cyclic_chunk(k, D);
-        std::printf("flat=%d nt=%d rg=%d rs=%d ps=%d gpp=%d chunks=%d rpb=%d bx=%d resident=%d lds=%d "
+        std::printf("flat=%d nt=%d rg=%d rs=%d ps=%d gpp=%d chunks=%d rpb=%d bx=%d resident=%d local=%d lds=%d "
                     "split=%d blocks=%lld order=%d strip_steps=%d strip_w=%d strip_threads=%d "
                     "bytes=%zu\n",
-                    k.flat, k.nt, k.rg, k.rs, k.ps, k.gpp, k.chunks, k.rpb, k.bx, k.resident,
+                    k.flat, k.nt, k.rg, k.rs, k.ps, k.gpp, k.chunks, k.rpb, k.bx, k.resident, k.resident_local,
                     lbm::held_lds_bytes(k.resident), k.split, blocks, blocks % (8LL * chunk) == 0, k.strip.steps, k.strip.w,
                     k.strip.threads, pop_bytes(ctx));
         lbm_destroy(ctx);

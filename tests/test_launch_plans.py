@@ -76,7 +76,9 @@ ENOUGH = {("D3Q95", "fp32s", "ab"): 300, ("D3Q95", "fp32s", "aa"): 230,
           ("D3Q15", "fp32s", "ab"): 600, ("D3Q15", "fp32s", "aa"): 600}
 
 
-def _enough(model, precision, streaming):
+def _enough(model, precision, streaming, nbytes):
+    if (model, precision, streaming) == ("D3Q95", "fp32s", "aa") and nbytes < 1 << 30:
+        return 300
     return ENOUGH.get((model, precision, streaming), 450 if precision == "fp32s" else 240)
 
 
@@ -104,20 +106,24 @@ def test_held_blocks_have_enough_cells(plans, model, extents, precision, streami
         for n in e:
             cells *= n
         per_block = cells / p["blocks"]
-        need = _enough(model, precision, streaming)
+        need = _enough(model, precision, streaming, p["bytes"])
         assert p["resident"] * per_block >= need, (e, p)
         assert p["resident"] <= 2 or (p["resident"] - 1) * per_block < need, (e, p)
     assert held > 0
 
 
-def test_packed_rows_of_float64_in_place_are_not_held(plans):
-    # 128^3 held 599 us per step, unlimited 591; 64x250x250 1155, 1138; only a block of one
-    # row of 192 (or half of one of 320 or 384) gains
-    cases = [("D3Q95", e, "fp64", "aa") for e in ((128, 128, 128), (64, 250, 250), (64, 251, 251),
-                                                  (128, 129, 129), (256, 256, 256))]
-    assert [p["resident"] for p in plans(cases)] == [0] * len(cases)
-    cases = [("D3Q95", e, "fp64", "aa") for e in ((192, 192, 192), (320, 200, 200), (384, 150, 150))]
-    assert [p["resident"] for p in plans(cases)] == [1] * len(cases)
+def test_in_place_steps_of_d3q95_are_held_apart(plans):
+    # the pushing step is held; the local one with it only where that was measured faster
+    push_only = [((128, 128, 128), "fp64"), ((64, 250, 250), "fp64"), ((256, 256, 256), "fp64"),
+                 ((192, 70, 60), "fp64"), ((400, 100, 100), "fp64"), ((200, 100, 100), "fp64"),
+                 ((57, 176, 86), "fp32s"), ((350, 50, 40), "fp32s"), ((320, 80, 60), "fp32s"),
+                 ((128, 128, 128), "fp32s")]
+    both = [((192, 192, 192), "fp64"), ((320, 200, 200), "fp64"), ((384, 150, 150), "fp64"),
+            ((256, 256, 256), "fp32s"), ((170, 145, 141), "fp32s")]
+    for (e, prec), p in zip(push_only, plans([("D3Q95", e, pr, "aa") for e, pr in push_only])):
+        assert p["resident"] > 0 and p["local"] == 0, (e, prec, p)
+    for (e, prec), p in zip(both, plans([("D3Q95", e, pr, "aa") for e, pr in both])):
+        assert p["resident"] > 0 and p["local"] == p["resident"], (e, prec, p)
 
 
 # Narrow 2D grids: (extent, held) where several steps per launch were measured faster than

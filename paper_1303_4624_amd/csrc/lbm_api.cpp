@@ -317,10 +317,11 @@ constexpr size_t kHeldInPlace = size_t{1} << 30;
 //     D3Q15 200^3         229   277  174 *163  164  168    -  172
 //     D3Q15 256x200x200   256   318  212 *207  211  210    -  215
 //     D3Q15 384x160x160   192   395  232  204 *202  208    -  210
-//   smaller sets, float64 (two blocks at least)
+//   smaller sets, float64 (two blocks at least, but see set_blocks)
 //     D3Q19 5x5x200000     25     -  751  540  449  377  334  331  *10
 //     D3Q19 11x11x60000   121   522 *392  414  430  462    -  439
-//     D3Q19 400x160x160   200   673 *536  560  567  581    -  581
+//     D3Q19 400x160x160   200   673  536  560  567  581    -  581
+//                         400  *516  527    -    -    -    -    -
 //     D3Q15 384x160x160   192   497 *406  417  422  421    -  425
 //     D3Q15 256x200x200   256   506 *415  417  420  422    -  423
 int held_cells(const lbm_ctx* ctx, BlockUse use) {
@@ -371,7 +372,7 @@ void set_blocks(const lbm_ctx* ctx, KParams& k, BlockUse use) {
     int flat_most = lbm::flat_block_limit(ctx->Q, ctx->prec);
     int pack_most = use == kAdjoint ? lbm::kPackAdjMaxBlock : lbm::kPackMaxBlock;
     bool held = false;
-    double least = 1;   // blocks where they are
+    int least = 1;   // blocks where they are
     if (few) {
         most = flat_most = pack_most = 64;
     } else if (k.nt && use != kAdjoint) {
@@ -395,17 +396,19 @@ void set_blocks(const lbm_ctx* ctx, KParams& k, BlockUse use) {
         cells = static_cast<double>(k.nx) * k.ny / k.gpp / k.chunks;
     } else {
         // a held row that its blocks would leave a tenth short of lanes takes
-        // larger ones (D3Q95 in place 192^3: 1115 us with 2 blocks of 128 a row,
-        // 1025 with one of 192)
-        const auto short_of = [&](int m) {
+        // larger ones, the first that do not, else those with the fewest lanes
+        // (D3Q95 in place 192^3: 1115 us with 2 blocks of 128 a row, 1025 with one
+        // of 192; 385x71x28 120 with 2 of 256, 106 with one of 448; 400x128x128 938
+        // with 4 of 128, 925; D2Q33 400x8000 136, 128)
+        const auto lanes = [&](int m) {
             const lbm::RowLaunch r = lbm::row_launch(k.nx, rows, m);
-            return 10LL * r.chunks * r.bx > 11LL * k.nx;
+            return r.chunks * r.bx;
         };
         int fit = most;
-        if (held && short_of(most)) {
+        if (held) {
             const int limit = lbm::step_max_threads(ctx->model, ctx->prec);
-            while (fit < limit && short_of(fit)) fit += 64;
-            if (short_of(fit)) fit = most;
+            for (int m = most; m <= limit && 10LL * lanes(fit) > 11LL * k.nx; m += 64)
+                if (lanes(m) < lanes(fit)) fit = m;
         }
         const lbm::RowLaunch rl = lbm::row_launch(k.nx, rows, fit);
         k.chunks = rl.chunks;
@@ -419,7 +422,11 @@ void set_blocks(const lbm_ctx* ctx, KParams& k, BlockUse use) {
         }
         cells = static_cast<double>(k.nx) * k.rpb / k.chunks;
     }
-    const double hold = held ? std::max(least, std::ceil(held_cells(ctx, use) / cells)) : 0.0;
+    // float64, two buffers: one of 400 cells does (D3Q19 400^2 x 100 211 us, two 219;
+    // in place 200, 199; D3Q15 in place 159, 156)
+    if (ctx->Q >= 19 && use == kSteps && cells >= 380) least = 1;
+    const double hold =
+        held ? std::max<double>(least, std::ceil(held_cells(ctx, use) / cells)) : 0.0;
     k.resident = hold <= lbm::kMaxHeld ? static_cast<int>(hold) : 0;
     k.resident_local = k.resident;
     if (ctx->Q >= 95 && use == kStepsInPlace) {

@@ -168,3 +168,21 @@ def test_block_order_switches_on_the_grids_of_the_gpu_test(plans, streaming):
     for (m, e, _, flat, packed), p in zip(ORDERED, plans(cases)):
         assert p["order"] == 1, (m, e, p)
         assert (p["flat"] == 1) == flat and (p["rpb"] > 1) == packed, (m, e, p)
+
+
+@pytest.mark.parametrize("model,extent,precision,most,limit", [
+    # most: the block size the held steps of the set start from, limit: the largest
+    ("D3Q95", (385, 71, 28), "fp32s", 256, 512), ("D3Q95", (400, 128, 128), "fp32s", 128, 512),
+    ("D3Q19", (769, 120, 120), "fp32s", 256, 512), ("D2Q33", (804, 9000), "fp32s", 256, 512),
+    ("D3Q95", (320, 80, 60), "fp32s", 256, 512), ("D3Q15", (1042, 100, 100), "fp32s", 256, 512),
+])
+def test_held_rows_take_the_blocks_with_the_fewest_idle_lanes(plans, model, extent, precision,
+                                                              most, limit):
+    p, = plans([(model, extent, precision, "aa")])
+    nx = extent[0]
+
+    def lanes(m):
+        chunks = -(-nx // m)
+        return chunks * (-(-(-(-nx // chunks)) // 64) * 64)
+    fewest = min(lanes(m) for m in range(most, limit + 1, 64))
+    assert p["resident"] > 0 and p["chunks"] * p["bx"] <= max(fewest, 1.1 * nx), p

@@ -184,8 +184,15 @@ int cyclic_chunk(const KParams& k, int D) {
 // Groups of a power of two of rows leave the last one partly empty; the
 // shortest that keeps the state within the padded rows' bytes (or, for states
 // that are small against the memory, within an eighth of its cells) is taken,
-// else the whole plane is one group.
+// else the whole plane is one group, up to kWholeCells: longer runs lie too far
+// apart, as in one array per population (us per step, one group against rows:
+// D2Q33 float64 96x62501 610, 539, in place 595, 515; D3Q95 float64 383x250x60
+// 1731, 1537, FP32-shifted in place 224x250x100 853, 815; 160x50x750, 8000 cells,
+// 1638, 1735).  So do rows of 29 to 31 cells of D3Q95 FP32-shifted with two buffers
+// where the plane's run is no multiple of a line: its stores would all start
+// inside one (31x33x9000 1766, 1507; in place 1289, 1488).
 constexpr long long kSmallState = 1LL << 30;   // bytes
+constexpr long long kWholeCells = 16 * lbm::kRunCells;
 
 void fill_layout(const lbm_ctx* ctx, KParams& k) {
     const long long bytes = static_cast<long long>(elem_bytes(ctx->prec));
@@ -204,11 +211,15 @@ void fill_layout(const lbm_ctx* ctx, KParams& k) {
             const bool pad = 16 * (lines * lbm::kRunAlign - rg * k.nx) <= rg * k.nx &&
                              (!whole || lines * lbm::kRunAlign <= by_rows || small);
             const long long ps = pad ? lines * lbm::kRunAlign : rg * k.nx;
+            const bool apart =
+                whole && (rg * k.nx > kWholeCells || (!ctx->aa && ctx->Q >= 95 && bytes == 4 &&
+                                                      k.nx > 28 && ps % lbm::kRunAlign != 0 &&
+                                                      !small));
             const long long plane = ps * gpp * ctx->Q * bytes;
             const bool fits = ps * gpp <= by_rows ||
                               (small && (whole || 8 * gpp * rg <= 9LL * k.ny));
             // the kernels address a plane (in 2D: the grid) with 32-bit byte offsets
-            if (!fits || plane >= (1LL << 32)) continue;
+            if (!fits || apart || plane >= (1LL << 32)) continue;
             k.flat = 1;
             k.rg = static_cast<int>(rg);
             k.rg_shift = whole ? 31 : sh;

@@ -186,3 +186,22 @@ def test_held_rows_take_the_blocks_with_the_fewest_idle_lanes(plans, model, exte
         return chunks * (-(-(-(-nx // chunks)) // 64) * 64)
     fewest = min(lanes(m) for m in range(most, limit + 1, 64))
     assert p["resident"] > 0 and p["chunks"] * p["bx"] <= max(fewest, 1.1 * nx), p
+
+
+def test_long_planes_are_stored_by_rows(plans):
+    # states past 1 GB whose rows leave no slack for a partly empty last group: one group of the
+    # whole plane up to 16384 cells, by rows past that; never more bytes than padded rows
+    flat = [("D3Q95", (160, 50, 750), "fp64", "ab"), ("D3Q95", (32, 150, 1250), "fp32s", "ab"),
+            ("D3Q19", (96, 50, 6250), "fp64", "aa"), ("D3Q95", (11, 11, 40000), "fp32s", "ab"),
+            ("D3Q95", (31, 33, 9000), "fp32s", "aa"), ("D3Q95", (28, 30, 9000), "fp32s", "ab")]
+    rows = [("D2Q33", (96, 62501), "fp64", "ab"), ("D2Q33", (224, 26786), "fp64", "aa"),
+            ("D3Q95", (383, 250, 60), "fp64", "ab"), ("D3Q95", (224, 250, 100), "fp32s", "aa"),
+            ("D3Q19", (160, 251, 600), "fp64", "ab"), ("D3Q95", (31, 33, 9000), "fp32s", "ab")]
+    for cases, want in ((flat, 1), (rows, 0)):
+        for (m, e, prec, st), p in zip(cases, plans(cases)):
+            assert p["flat"] == want, (m, e, prec, st, p)
+            align = 32 if e[0] >= 32 else 1
+            padded = -(-e[0] // align) * align * Q[m] * (4 if prec == "fp32s" else 8)
+            for n in e[1:]:
+                padded *= n
+            assert (1 << 30) < p["bytes"] <= padded, (m, e, prec, st, p)

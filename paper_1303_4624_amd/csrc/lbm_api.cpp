@@ -252,7 +252,11 @@ void fill_layout(const lbm_ctx* ctx, KParams& k) {
     // 80.6, 78.4; 64x64x160 (498 MB) 100.6, 101.7; 128x128x64 (797 MB) 157.9,
     // 162.7; float64 64x64x32 (199 MB) 38.4, 31.9; in place 64x64x128 (199 MB)
     // 64.9, 58.7, 64x64x160 (249 MB) 75.8, 74.4, float64 128^3 D3Q19 (319 MB) 93.6,
-    // 95.6 and 128x128x64 (398 MB) 129.9, 134.2; D2Q33 512^2 15.0, 12.5.
+    // 95.6 and 128x128x64 (398 MB) 129.9, 134.2.  The smaller sets change over earlier:
+    // D2Q33 512^2 15.0, 12.5; 1000x1000 (264 MB) 53.1, 46.8; 1000x1200 (317) 59.4, 55.0;
+    // 1000x1311 (346) 64.4, 64.1; 1000x1450 (383) 70.5, 74.4; float64 1024x700 (378)
+    // 67.4, 70.7; D3Q19 FP32-shifted 128x128x140 (349) 61.0, 60.7; 128x128x156 (388) 67.1,
+    // 69.8; float64 128x128x76 (379) 66.3, 68.3.
     const long long state = static_cast<long long>(k.gs) * k.gpp * k.nz * bytes;
     // Between those, D3Q95 with two buffers of 16 to 40 MB: the L2s (8 of 4 MB)
     // hold a whole step's output and write it back at the kernel's end, which
@@ -261,7 +265,9 @@ void fill_layout(const lbm_ctx* ctx, KParams& k) {
     // 40^3, 49 MB: 17.9, 13.5).  The smaller sets gain nothing (D3Q15 64^3, 31
     // MB: 7.2 against 6.6 us).
     const long long moved = ctx->aa ? state : 2 * state;
-    k.nt = moved > (ctx->aa ? lbm::kCachedStateInPlace : lbm::kCachedState) ||
+    const long long cached = ctx->aa ? lbm::kCachedStateInPlace
+                             : ctx->Q >= 95 ? lbm::kCachedState : lbm::kCachedStateSmallSets;
+    k.nt = moved > cached ||
            (!ctx->aa && ctx->Q >= 95 && moved > lbm::kL2StateLo && moved <= lbm::kL2StateHi);
 }
 

@@ -58,6 +58,7 @@ constexpr int kFlatCells = 384;
 // Bytes of populations up to which a step's stores stay in the cache (256 MB
 // shared by all XCDs); see fill_layout.
 constexpr long long kCachedState = 384LL << 20;
+constexpr long long kCachedStateSmallSets = 336LL << 20;   // Q < 95
 constexpr long long kCachedStateInPlace = 256LL << 20;   // one buffer
 constexpr long long kL2StateLo = 16LL << 20;
 constexpr long long kL2StateHi = 40LL << 20;

@@ -205,3 +205,15 @@ def test_long_planes_are_stored_by_rows(plans):
             for n in e[1:]:
                 padded *= n
             assert (1 << 30) < p["bytes"] <= padded, (m, e, prec, st, p)
+
+
+def test_stores_of_the_smaller_sets_leave_the_cache_earlier(plans):
+    # bytes of both buffers, measured faster with plain and with non-temporal stores
+    plain = [("D2Q33", (1000, 1200), "fp32s"), ("D2Q33", (1000, 600), "fp64"),
+             ("D3Q19", (128, 128, 66), "fp64"), ("D3Q95", (64, 64, 128), "fp32s"),
+             ("D3Q95", (235, 64, 16), "fp64")]
+    past = [("D2Q33", (1000, 1450), "fp32s"), ("D2Q33", (1024, 700), "fp64"),
+            ("D3Q19", (128, 128, 156), "fp32s"), ("D3Q19", (128, 128, 76), "fp64"),
+            ("D3Q95", (64, 64, 160), "fp32s")]
+    assert [p["nt"] for p in plans([c + ("ab",) for c in plain])] == [0] * len(plain)
+    assert [p["nt"] for p in plans([c + ("ab",) for c in past])] == [1] * len(past)

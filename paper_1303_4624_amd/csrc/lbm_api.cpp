@@ -188,9 +188,11 @@ int cyclic_chunk(const KParams& k, int D) {
 // apart, as in one array per population (us per step, one group against rows:
 // D2Q33 float64 96x62501 610, 539, in place 595, 515; D3Q95 float64 383x250x60
 // 1731, 1537, FP32-shifted in place 224x250x100 853, 815; 160x50x750, 8000 cells,
-// 1638, 1735).  So do rows of 29 to 31 cells of D3Q95 FP32-shifted with two buffers
-// where the plane's run is no multiple of a line: its stores would all start
-// inside one (31x33x9000 1766, 1507; in place 1289, 1488).
+// 1638, 1735), unless rows would leave half the lanes idle and all runs off the
+// line grid (D3Q15 float64 in place 30x1219x445 691, 852; D2Q33 20x300001 592, 709,
+// but 31x200001 623, 567).  By rows are also 29 to 31 cells of D3Q95 FP32-shifted
+// with two buffers where the plane's run is no multiple of a line: its stores
+// would all start inside one (31x33x9000 1766, 1507; in place 1289, 1488).
 constexpr long long kSmallState = 1LL << 30;   // bytes
 constexpr long long kWholeCells = 16 * lbm::kRunCells;
 
@@ -212,9 +214,9 @@ void fill_layout(const lbm_ctx* ctx, KParams& k) {
                              (!whole || lines * lbm::kRunAlign <= by_rows || small);
             const long long ps = pad ? lines * lbm::kRunAlign : rg * k.nx;
             const bool apart =
-                whole && (rg * k.nx > kWholeCells || (!ctx->aa && ctx->Q >= 95 && bytes == 4 &&
-                                                      k.nx > 28 && ps % lbm::kRunAlign != 0 &&
-                                                      !small));
+                whole && ((k.nx >= (ctx->D == 3 ? 32 : 24) && rg * k.nx > kWholeCells) ||
+                          (!ctx->aa && ctx->Q >= 95 && bytes == 4 && k.nx > 28 &&
+                           ps % lbm::kRunAlign != 0 && !small));
             const long long plane = ps * gpp * ctx->Q * bytes;
             const bool fits = ps * gpp <= by_rows ||
                               (small && (whole || 8 * gpp * rg <= 9LL * k.ny));

@@ -193,8 +193,10 @@ def test_long_planes_are_stored_by_rows(plans):
     # whole plane up to 16384 cells, by rows past that; never more bytes than padded rows
     flat = [("D3Q95", (160, 50, 750), "fp64", "ab"), ("D3Q95", (32, 150, 1250), "fp32s", "ab"),
             ("D3Q19", (96, 50, 6250), "fp64", "aa"), ("D3Q95", (11, 11, 40000), "fp32s", "ab"),
-            ("D3Q95", (31, 33, 9000), "fp32s", "aa"), ("D3Q95", (28, 30, 9000), "fp32s", "ab")]
-    rows = [("D2Q33", (96, 62501), "fp64", "ab"), ("D2Q33", (224, 26786), "fp64", "aa"),
+            ("D3Q95", (31, 33, 9000), "fp32s", "aa"), ("D3Q95", (28, 30, 9000), "fp32s", "ab"),
+            ("D3Q15", (30, 1219, 445), "fp64", "aa"), ("D2Q33", (20, 300001), "fp64", "aa")]
+    rows = [("D2Q33", (96, 62501), "fp64", "ab"), ("D2Q33", (31, 200001), "fp64", "ab"),
+            ("D2Q33", (224, 26786), "fp64", "aa"),
             ("D3Q95", (383, 250, 60), "fp64", "ab"), ("D3Q95", (224, 250, 100), "fp32s", "aa"),
             ("D3Q19", (160, 251, 600), "fp64", "ab"), ("D3Q95", (31, 33, 9000), "fp32s", "ab")]
     for cases, want in ((flat, 1), (rows, 0)):

@@ -374,7 +374,8 @@ int held_cells(const lbm_ctx* ctx, BlockUse use) {
 // per step (the mean of both), unlimited, push held, both held: D3Q95 float64
 // 192x70x60 218, 210, 228; 256x64x80 357, 353, 374; 128^3 588, 586, 600; 400x100x100
 // 1249, 1189, 1172; 512x100x100 1507, 1469, 1482; flat 150x100x60 250, 241, 254; 200x100x100
-// 606, 579, 586; rows of one block of 192, or of two, both from 1.5 GB (192x128x100
+// 606, 579, 586; flat with runs off the line grid both (17x652x269 958, 938, 899;
+// 11x11x40000 1417, 1401, 1323); rows of one block of 192, or of two, both from 1.5 GB (192x128x100
 // 741, 713, 711; 320x100x100 994, 942, 922; below 384x60x44 293, 277, 292); FP32-shifted
 // below 1 GB 57x176x86 136, 126, 126; 300x80x60 194, 187, 200; 128^3 271, 269, 281;
 // 320x80x60 227, 219, 220; from 1 GB two blocks of 128 in both (256x128x128 647, 597,
@@ -450,8 +451,10 @@ void set_blocks(const lbm_ctx* ctx, KParams& k, BlockUse use) {
     k.resident_local = k.resident;
     if (ctx->Q >= 95 && use == kStepsInPlace) {
         const size_t bytes = pop_bytes(ctx);
-        const bool local = f64 ? !k.flat && k.bx == 192 && 2 * bytes >= 3 * kHeldInPlace
-                               : bytes >= kHeldInPlace;
+        const bool off_lines = k.flat && k.ps % (lbm::kLineBytes / 8) != 0;
+        const bool local = !f64      ? bytes >= kHeldInPlace
+                           : k.flat ? off_lines
+                                    : k.bx == 192 && 2 * bytes >= 3 * kHeldInPlace;
         if (!local) k.resident_local = 0;
     }
     set_divisors(k);

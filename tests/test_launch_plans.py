@@ -118,7 +118,7 @@ def test_in_place_steps_of_d3q95_are_held_apart(plans):
                  ((192, 70, 60), "fp64"), ((400, 100, 100), "fp64"), ((200, 100, 100), "fp64"),
                  ((57, 176, 86), "fp32s"), ((350, 50, 40), "fp32s"), ((320, 80, 60), "fp32s"),
                  ((128, 128, 128), "fp32s")]
-    both = [((192, 192, 192), "fp64"), ((320, 200, 200), "fp64"), ((384, 150, 150), "fp64"),
+    both = [((17, 652, 269), "fp64"), ((192, 192, 192), "fp64"), ((320, 200, 200), "fp64"), ((384, 150, 150), "fp64"),
             ((256, 256, 256), "fp32s"), ((170, 145, 141), "fp32s")]
     for (e, prec), p in zip(push_only, plans([("D3Q95", e, pr, "aa") for e, pr in push_only])):
         assert p["resident"] > 0 and p["local"] == 0, (e, prec, p)

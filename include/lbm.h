@@ -38,10 +38,12 @@
  *    its runs.  Rows that are a multiple of 64 cells, or long: r = nx rounded
  *    up to a multiple of 32, p = g*r, in 3D runs of about 1024 cells (g = 1 in
  *    2D); else r = nx and p = g*nx rounded up to a multiple of 32 where that
- *    adds little (two-buffer streaming; with
+ *    adds little, unless the groups that fit would be whole planes of long runs
+ *    or of 4 GiB and more, which are kept by rows too (two-buffer streaming; with
  *    LBM_STREAM_AA the slot of a value alternates, see lbm_set_streaming).
  *    The layout is internal to the library (sizes from
- *    lbm_workspace_bytes) and may differ between its builds.  In
+ *    lbm_workspace_bytes) and may differ between its builds: a buffer written
+ *    by one build of the library is not read by another.  In
  *    LBM_FP64 each element is the double f*_i.  In LBM_FP32_SHIFTED each
  *    element is the float g_i = f*_i - w_i*rho0.  lbm_set_populations and
  *    lbm_get_populations exchange float64 f* in the order [Q][N] (element
@@ -259,8 +261,9 @@ int lbm_get_populations(lbm_ctx* ctx, double* f);
  * kernel: gather f_i(x, t + 1) = f*_i(x - e_i, t) (periodic, any extent),
  * moments, 4th-order equilibrium, BGK relaxation, coalesced store of
  * f*(x, t + 1).  Narrow 2D grids (two buffers) take up to 7 steps of a call in
- * one kernel where that is expected to be faster (up to about 20 cells across in
- * float64, 36 in FP32-shifted), with the same results bit for bit.  An even number of steps leaves the state
+ * one kernel where that is expected to be faster (up to about 20 cells across
+ * in float64, 36 in FP32-shifted; planned again by lbm_set_fixed_planes), with
+ * the same results bit for bit.  An even number of steps leaves the state
  * in the buffer it was in, an odd number in the other one.  Asynchronous.
  */
 int lbm_step(lbm_ctx* ctx, int n);
@@ -270,17 +273,17 @@ int lbm_step(lbm_ctx* ctx, int n);
  * the forward steps hand out their blocks, and keeping the faster order for
  * the steps that follow.
  *
- * The blocks of a forward step (two-buffer or in place) are dispatched
- * round-robin over the 8 XCDs of the device.  Order 0 (the default) gives each XCD a contiguous
- * range of rows; order 1 gives the XCDs one slab of the slowest axis (a
- * z-plane in 3D, a row in 2D) in turn.  Which is faster depends on where in
+ * The blocks of a forward step (two-buffer or in place) are dispatched round-
+ * robin over the 8 XCDs of the device.  Order 0 (the default) gives each XCD a
+ * contiguous range of rows; order 1 gives the XCDs one slab of the slowest axis
+ * (a z-plane in 3D, a row in 2D) in turn.  Which is faster depends on where in
  * HBM the bound buffers lie (measured on D3Q95 FP32-shifted 384^3: order 1
- * 0.4-1.3 % faster on some placements, 1.5-2 % slower on others; in place
- * 0.5 % faster on the placements measured).  The
- * order only decides which blocks run where: every step, the checkpointed
- * forward run and the recomputation in lbm_adjoint give bit-identical
- * results under both, and the kernels that sum across blocks (conservation,
- * adjoint) keep order 0, so their rounding does not depend on it.
+ * 0.4-1.3 % faster on some placements, 1.5-2 % slower on others; in place 0.5 %
+ * faster on the placements measured).  The order only decides which blocks run
+ * where: every step, the checkpointed forward run and the recomputation in
+ * lbm_adjoint give bit-identical results under both, and the kernels that sum
+ * across blocks (conservation, adjoint) keep order 0, so their rounding does
+ * not depend on it.
  *
  *   n       : steps to run (>= 0); the result equals lbm_step(ctx, n) bit
  *             for bit.  The steps alternate the two orders (in place: per
@@ -384,11 +387,13 @@ int lbm_set_fixed_planes(lbm_ctx* ctx, int n_lo, int n_hi, const double* state_l
  * launches of `steps` steps once, later calls replay the graph for every full
  * block of `steps` steps and launch the remainder one by one.  Launch-bound
  * small grids (the shock tube) gain; the arithmetic and results are the same
- * bit for bit.  steps must be even (the buffers and storage form return to
- * their state after an even count), 0 turns replay off (the default).  The
- * graph is rebuilt after lbm_bind, lbm_set_omega or lbm_set_fixed_planes.
- * Needs a non-null stream (LBM_E_UNSUPPORTED otherwise); LBM_E_INVALID for
- * odd or negative steps.  Graphs hold no memset nodes.
+ * bit for bit.  A graph holds one launch per step: narrow 2D grids, of which
+ * lbm_step takes several steps in one launch, are as fast or faster without.
+ * steps must be even (the buffers and storage form return to their state after
+ * an even count), 0 turns replay off (the default).  The graph is rebuilt after
+ * lbm_bind, lbm_set_omega or lbm_set_fixed_planes.  Needs a non-null stream
+ * (LBM_E_UNSUPPORTED otherwise); LBM_E_INVALID for odd or negative steps.
+ * Graphs hold no memset nodes.
  */
 int lbm_set_graph_steps(lbm_ctx* ctx, int steps);
 
@@ -421,7 +426,9 @@ int lbm_run_checkpointed(lbm_ctx* ctx, int n, int k, int keep, void* ckpt, size_
  * lbm_restore_checkpoint - resume a run from a checkpoint buffer filled by
  * lbm_run_checkpointed(n, k, keep) of a context with the same model, grid,
  * precision and rho0 (checkpoint/resume; the state is the one the update
- * rule advances).
+ * rule advances).  The buffer is in the layout of the library that filled it
+ * and holds no mark of it: one that was saved to a file is read back only by
+ * the same build.  To keep a state across builds, save lbm_get_populations.
  *   slot : 0 .. ceil(n/k) - 1 restores the stored state at t = slot*k;
  *          ceil(n/k) restores the final state at t = n.
  * The snapshot is copied into the bound populations (in place: into the

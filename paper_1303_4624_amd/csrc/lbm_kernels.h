@@ -190,7 +190,9 @@ struct Cell {
 // a small run by much (fill_layout in lbm_api.cpp); a group holds
 // gs = Q*ps elements and a plane zs (KParams).  A step then writes contiguous
 // runs and reads Q runs from the few source rows around it.
-//   by rows : rs = nx rounded up to whole lines, rg = 1 or 2, ps = rg*rs.
+//   by rows : rs = nx rounded up to whole lines; in 3D rg is the power of two
+//             dividing ny whose rows reach kRunCells (else the largest that
+//             divides it), in 2D 1; ps = rg*rs.
 //   flat    : rs = nx (no gaps between the rows of a run), rg a power of two
 //             or the whole plane, ps = rg*nx rounded up to whole lines.
 //
@@ -810,8 +812,11 @@ __device__ __forceinline__ void relax_with(const KParams& k, const typename P::S
 // conserved up to the rounding of each cell's own values.
 //
 // HOLD: rows inside the held planes of the slowest axis (the fixed end
-// planes of the shock tube) store f^eq of the held state instead; the test
-// is uniform over a block.
+// planes of the shock tube) store f^eq of the held state instead.  The test is
+// uniform over a wave by rows, over a block on flat groups in 3D, and per lane on
+// flat groups in 2D, where the rows of a group may lie on both sides of a held
+// plane's edge.
+//
 // The stored step moments of a cell on a held plane: those of the held state.
 template <class M, class P>
 __device__ __forceinline__ void store_held_moments(const KParams& k, const Cell& cl,

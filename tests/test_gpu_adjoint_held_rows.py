@@ -1,8 +1,9 @@
-"""Temperature gradient with held planes where the grid is stored by rows: rows
-of one wave, rows that end inside a wave
-and rows whose last wave is mostly surplus lanes.  Against the oracle's autograd;
-float64 1e-11 (the bar of the gradients in row groups), FP32-shifted 1e-5 (of the held tubes) of the largest
-gradient)."""
+"""Temperature gradient with held planes where the grid is stored by rows: rows of
+one wave, rows that end inside a wave, and rows whose last wave is mostly surplus
+lanes.  Against the oracle's autograd: float64 within 1e-11 of the largest gradient
+(the bar of the gradients in row groups), FP32-shifted within 1e-5 (that of the held
+tubes).
+"""
 import numpy as np
 import pytest
 import torch

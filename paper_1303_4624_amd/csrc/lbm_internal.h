@@ -161,7 +161,6 @@ struct KParams {
     int bx;                   // threads per block (multiple of 64)
     int split;                // 1: kSplit blocks share the cells of one (two buffers)
     int resident;             // blocks a CU holds at once (0: as many as fit)
-    int resident_local;       // the same of the in-place step that stores to its own cells
     FastDiv by_nx, by_ny, by_gpp, by_chunks;
     unsigned inv_nx, inv_ny, inv_nz;   // 65536 / n + 1 (axes of at most kMaxDisp cells)
     int reverse;              // 1: this launch takes the blocks from the last to the first
@@ -180,6 +179,10 @@ struct KParams {
     FixedState hold[2];
     int steps;                // steps of this launch (> 1: in strips)
     StripParams strip;
+    // `resident` of the in-place step that stores to its own cells; read by the host
+    // only, so it stands after what kernels read (in the middle it moved the weights by
+    // a word and their loads apart: D3Q95 float64 512x4x4 7.76 against 7.62 us per step)
+    int resident_local;
 };
 
 // Launch geometry of the row-blocked kernels: one grid row (fixed y, z) is

@@ -533,8 +533,12 @@ def summarize_profiles(prof_dir: str, grid: int = 384, steps: int = 0) -> str:
 
 # Side measurements after the headline (all by default; --only picks some).
 _MODEL_QD = {"D2Q33": (33, 2), "D3Q95": (95, 3), "D3Q19": (19, 3), "D3Q15": (15, 3)}
-# kernels launched one lane per cell over whole rows padded to 64 lanes
+# kernels launched one lane per cell over whole rows padded to 64 lanes, or over
+# flat row groups
 _ROW_KERNELS = ("k_step", "k_step_aa", "k_adjoint")
+# kernels whose launches tell nothing of the cells: grid-stride sums, the streaming
+# copy, steps in strips and steps that several blocks share
+_OTHER_KERNELS = ("k_conservation", "k_stream_copy", "k_steps_strip", "k_step_split")
 # kernels launched one lane per cell over ceil(N / 256) blocks of 256
 _FLAT_KERNELS = ("k_init", "k_moments", "k_to_ab", "k_from_ab", "k_set_pop", "k_get_pop",
                  "k_lambda_init", "k_dT_init")
@@ -568,6 +572,8 @@ def _alg_bytes_per_cell(kernel, model, prec, flags):
     Q, D = _MODEL_QD[model]
     b = 8 if prec == "F64" else 4
     mom = (D + 2) * b
+    if kernel in ("k_steps_strip", "k_step_split"):   # a strip launch takes several steps
+        return 2 * Q * b
     if kernel == "k_step":                      # STORE_MOM, HOLD, POP
         sm, _, pop = (flags + (0, 0, 1))[:3]
         return Q * b + (Q * b if pop else 0) + (mom if sm else 0)
@@ -611,19 +617,19 @@ def _lane_cells():
 
 def _walk_dispatches(rows, grid_of):
     """Yield (row, instance, workload, cells, algorithmic bytes) for the
-    library's kernels in dispatch order; a grid-stride launch (the
-    conservation sums) and the streaming copy take the workload of the
-    launch before them."""
+    library's kernels in dispatch order; launches whose lanes name no
+    workload (_OTHER_KERNELS, flat row groups) take that of the launch before
+    them."""
     lanes = _lane_cells()
     cur = (None, None)
     for r in sorted(rows, key=lambda r: int(r["Dispatch_Id"])):
         kernel, model, prec, flags = _instance(r["Kernel_Name"])
         grid = grid_of(r)
         if kernel in _ROW_KERNELS:
-            cells, label = lanes.get(("row", grid), (None, None))
+            cells, label = lanes.get(("row", grid), cur)
         elif kernel in _FLAT_KERNELS:
             cells, label = lanes.get(("flat", grid), (None, None))
-        elif kernel in ("k_conservation", "k_stream_copy"):
+        elif kernel in _OTHER_KERNELS:
             cells, label = cur
         else:
             continue

@@ -364,7 +364,8 @@ int held_cells(const lbm_ctx* ctx, BlockUse use) {
 // read and write their own places in it at once, and which too few do not fill:
 // a CU is held to the fewest blocks that have held_cells() cells.  us per step,
 // unlimited against held, on the same buffers: D3Q95 FP32-shifted one block
-// of 512 or a 384-cell row (128^3 292, 281; 256^3 2260, 2188; 384^3 7770, 7505;
+// of 512 or a 384-cell row (128^3 292, 281; 256^3 2260, 2188; 384^3 7770, 7505 where
+// the buffers lie badly in HBM, the same within 1 % where they lie well (7.1-7.2 ms);
 // 200^3 1144, 1105), float64 one of 256 (256^3 4468, 4315; 150^3 937, 898); D2Q33
 // FP32-shifted one of 512 (2393x3579 403, 388; 8192^2 2914, 2867), float64 two of
 // 256 (814, 788); D3Q19 FP32-shifted two of 256 (256^3 438, 416), float64 the same
